@@ -24,6 +24,7 @@
 #include <cstring>
 
 #include "fw_kernels.h"
+#include "fw_requests.h"
 #include "fw_wave_sampler.h"
 
 namespace fw {
@@ -510,38 +511,6 @@ __device__ __forceinline__ uint64_t shfl64(uint64_t v, int src) {
   return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
 }
 
-// Request access: a single request passed by value, or a table of requests
-// (binary search of the query-count prefix maps a global index to its
-// request).
-template <bool MULTI>
-struct Reqs {
-  ReqDesc one;
-  ReqTable tab;
-  __device__ __forceinline__ uint64_t total() const { return MULTI ? tab.total : one.n; }
-  __device__ __forceinline__ uint32_t find(uint64_t q) const {
-    if (!MULTI) return 0;
-    uint32_t lo = 0, hi = tab.nreq;  // last r with prefix[r] <= q
-    while (hi - lo > 1) {
-      const uint32_t mid = (lo + hi) / 2;
-      if (tab.prefix[mid] <= q)
-        lo = mid;
-      else
-        hi = mid;
-    }
-    return lo;
-  }
-  __device__ __forceinline__ uint64_t first(uint32_t r) const {
-    return MULTI ? tab.prefix[r] : 0;
-  }
-  __device__ __forceinline__ ReqDesc get(uint32_t r) const { return MULTI ? tab.reqs[r] : one; }
-};
-
-// Served form: a retired query adds its realised hops to its request's
-// counter (one atomic per query).
-__device__ __forceinline__ void count_steps(const ReqDesc& R, uint32_t hops) {
-  if (R.steps != nullptr && hops != 0) atomicAdd(R.steps, (unsigned long long)hops);
-}
-
 // Eight wavefronts per SIMD (64 VGPRs): the walk is bound by the latency of
 // dependent loads (offsets, then the slice, then the LDS membership probes),
 // so occupancy pays more than the few per-hop register spills it costs.
@@ -765,6 +734,11 @@ k_walk_persistent(
 
 __global__ void k_reset_counter(uint64_t* p) { *p = 0; }
 
+hipError_t reset_counter(uint64_t* head, hipStream_t stream) {
+  hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(1), 0, stream, head);
+  return hipGetLastError();
+}
+
 template <int ALGO, bool W, bool MULTI>
 static hipError_t go(const DevGraph& g, const Reqs<MULTI>& rq, uint32_t* status, uint64_t* head,
                      const TuneCfg& cfg, unsigned blocks, hipStream_t stream) {
@@ -781,20 +755,21 @@ static hipError_t launch_any(int algo, const DevGraph& g, const Reqs<MULTI>& rq,
   if (c.tiny_max > 16 || c.wgs_per_cu == 0 || c.hash_cells < 64 ||
       (c.hash_cells & (c.hash_cells - 1)) || head == nullptr)
     return hipErrorInvalidValue;
+  const bool wt = g.w != nullptr;
+  // Unit weights: nothing to sum, a lane per query.
+  if (!wt && (algo == kDeepWalk || algo == kPPR))
+    return launch_uniform<MULTI>(algo, g, rq, status, head, num_cus, c.wgs_per_cu, n, stream);
   uint64_t blocks = (uint64_t)num_cus * c.wgs_per_cu;
   const uint64_t per_block = (kBlock / kWave) * kGroups;
   const uint64_t need = (n + per_block - 1) / per_block;
   if (blocks > need) blocks = need;
   if (blocks == 0) blocks = 1;
-  hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(1), 0, stream, head);
-  hipError_t e = hipGetLastError();
+  const hipError_t e = reset_counter(head, stream);
   if (e != hipSuccess) return e;
-  const bool wt = g.w != nullptr;
   const unsigned b = (unsigned)blocks;
   switch (algo) {
     case kDeepWalk:
-      return wt ? go<kDeepWalk, true>(g, rq, status, head, c, b, stream)
-                : go<kDeepWalk, false>(g, rq, status, head, c, b, stream);
+      return go<kDeepWalk, true>(g, rq, status, head, c, b, stream);
     case kNode2Vec:
       return wt ? go<kNode2Vec, true>(g, rq, status, head, c, b, stream)
                 : go<kNode2Vec, false>(g, rq, status, head, c, b, stream);
@@ -802,8 +777,7 @@ static hipError_t launch_any(int algo, const DevGraph& g, const Reqs<MULTI>& rq,
       return wt ? go<kMetaPath, true>(g, rq, status, head, c, b, stream)
                 : go<kMetaPath, false>(g, rq, status, head, c, b, stream);
     case kPPR:
-      return wt ? go<kPPR, true>(g, rq, status, head, c, b, stream)
-                : go<kPPR, false>(g, rq, status, head, c, b, stream);
+      return go<kPPR, true>(g, rq, status, head, c, b, stream);
     default:
       return hipErrorInvalidValue;
   }
