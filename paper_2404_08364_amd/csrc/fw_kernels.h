@@ -20,6 +20,7 @@ struct TuneCfg {
                         // weight times a factor is one 24-bit multiply
   uint32_t sparse_ratio;  // persistent node2vec: a hop with d(cur) >= ratio *
                           // d(prev) looks N(prev)'s keys up in N(cur) (0: never)
+  uint32_t hub_buckets;   // set per launch: buckets of the workgroup's hub cache
 };
 
 // max_w * max_f < 2^24: the product of a weight and a factor fits 32 bits

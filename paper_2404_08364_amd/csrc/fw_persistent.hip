@@ -19,10 +19,14 @@
 // while N(prev) is at most 64x N(cur), a merge of the two sorted rows (each
 // 256-entry chunk of N(cur) stages the window of N(prev) that holds its value
 // range into LDS and searches it there); when N(prev) is much larger than
-// N(cur), binary search of the sorted row in global memory.  No global memory
-// beyond the inputs, the output paths and one head counter is used.
+// N(cur), binary search of the sorted row in global memory.  The group totals
+// of hub rows stay in LDS for the workgroup's later visits (fw_hub_cache.h).
+// No global memory beyond the inputs, the output paths and one head counter is
+// used.
+#include <algorithm>
 #include <cstring>
 
+#include "fw_hub_cache.h"
 #include "fw_kernels.h"
 #include "fw_requests.h"
 #include "fw_wave_sampler.h"
@@ -53,7 +57,9 @@ constexpr uint64_t kSparseMinDegree = 2048;
 // 1330 ms; Chung-Lu 227M node2vec, 1M queries, 7157, 7084, 7021 and 6992 ms.
 constexpr uint64_t kSearchRatio = 64;
 constexpr int kGroupLanes = 16;
-constexpr int kBlock = 256;  // threads per workgroup (4 wavefronts)
+constexpr int kMaxBlock = 1024;  // threads per workgroup
+constexpr size_t kCuLds = 160 * 1024;
+constexpr size_t kLdsGrain = 1280;  // LDS is handed out in these steps
 
 __device__ __forceinline__ uint32_t log2_ceil(uint64_t x) {
   uint32_t b = 0;
@@ -414,12 +420,14 @@ __device__ __forceinline__ uint32_t row_lower_bound(const uint32_t* __restrict__
 template <class E>
 __device__ __forceinline__ uint64_t sparse_prev_group_totals(const E& ev, const QuadSlice& s,
                                                              const GroupSplit& sp,
-                                                             const Table& tb, int lane) {
-  // Raw totals.
+                                                             const Table& tb, int lane,
+                                                             const Hubs& hubs) {
+  // Raw totals (weighted rows: streamed, or kept from an earlier visit).
   const char* __restrict__ wrun = reinterpret_cast<const char*>(ev.w + s.a);
   auto quad_raw = [wrun](uint32_t q) { return *reinterpret_cast<const uint4*>(wrun + q * 16u); };
   uint64_t raw = 0;
-  if (ev.w != nullptr) {
+  if (ev.w != nullptr && hubs.find(s.d, raw)) {
+  } else if (ev.w != nullptr) {
     for (uint32_t g = 0; g < sp.groups; ++g) {
       const uint32_t gb = g * sp.gsz;
       const uint32_t ge = min(gb + sp.gsz, s.nq);
@@ -439,6 +447,7 @@ __device__ __forceinline__ uint64_t sparse_prev_group_totals(const E& ev, const 
       const uint64_t tot = wave_sum(acc);
       if ((uint32_t)lane == g) raw = tot;
     }
+    hubs.keep(s.d, raw);
   } else if ((uint32_t)lane < sp.groups) {
     const uint32_t gb = (uint32_t)lane * sp.gsz;
     const uint32_t ge = min(gb + sp.gsz, s.nq);
@@ -515,7 +524,7 @@ __device__ __forceinline__ uint64_t shfl64(uint64_t v, int src) {
 // dependent loads (offsets, then the slice, then the LDS membership probes),
 // so occupancy pays more than the few per-hop register spills it costs.
 template <int ALGO, bool WEIGHTED, bool MULTI>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void
+__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void
 k_walk_persistent(
     DevGraph g, Reqs<MULTI> rq, uint32_t* __restrict__ status, uint64_t* __restrict__ head,
     TuneCfg cfg) {
@@ -526,6 +535,16 @@ k_walk_persistent(
   tb.cells = cfg.hash_cells;
   tb.base = (threadIdx.x / kWave) * cfg.hash_cells;
   tb.kind = 0;
+  // After the wavefronts' regions: the workgroup's hub totals.
+  Hubs hubs;
+  hubs.base = (hub_ptr)(fw_dyn_lds + (blockDim.x / kWave) * cfg.hash_cells);
+  hubs.buckets = cfg.hub_buckets;
+  hubs.cur = kEnd;
+  hubs.want = 0;
+  if (hubs.buckets != 0) {
+    clear_hubs(hubs.base, hubs.buckets);
+    __syncthreads();  // the only barrier: no wavefront waits for another below
+  }
 
   // This group's query (identical in the 16 lanes of the group): request r,
   // index in the request, vertex state.
@@ -661,6 +680,8 @@ k_walk_persistent(
       const uint64_t u = philox_draw(R.seed, R.qid_base + qid, t);
       auto ev = base_eval<ALGO, WEIGHTED, MemberAny>(g, prm, o, prev, t);
       ev.narrow = cfg.narrow != 0;
+      hubs.cur = readlane32(s_cur, src);
+      hubs.want = ev.want;
       ev.mem.mode = tb.kind == 1 ? 1 : 0;
       ev.mem.base = tb.base;
       ev.mem.bmask = tb.bmask;
@@ -679,7 +700,7 @@ k_walk_persistent(
         const GroupSplit sp(qs.nq);
         const bool sparse = tb.kind == 3;
         uint64_t gcur = 0;
-        const uint64_t mine = sparse ? sparse_prev_group_totals(ev, qs, sp, tb, lane)
+        const uint64_t mine = sparse ? sparse_prev_group_totals(ev, qs, sp, tb, lane, hubs)
                                      : merge_group_totals(ev, qs, sp, tb, lane, gcur);
         const uint64_t incl = wave_incl_scan(mine);
         const uint64_t total = readlane64(incl, kWave - 1);
@@ -707,8 +728,10 @@ k_walk_persistent(
             idx = (int64_t)wave_locate(ev, qs, lo, len, r);
           }
         }
-      } else {
+      } else if constexpr (ALGO == kNode2Vec) {
         idx = wave_pick(ev, o, d, u);
+      } else {
+        idx = wave_pick(ev, o, d, u, hubs);
       }
       uint32_t* row = R.out + qid * ((uint64_t)length + 1);
       const bool mine = grp == src / kGroupLanes;
@@ -741,17 +764,19 @@ hipError_t reset_counter(uint64_t* head, hipStream_t stream) {
 
 template <int ALGO, bool W, bool MULTI>
 static hipError_t go(const DevGraph& g, const Reqs<MULTI>& rq, uint32_t* status, uint64_t* head,
-                     const TuneCfg& cfg, unsigned blocks, hipStream_t stream) {
-  const size_t lds = (size_t)cfg.hash_cells * sizeof(uint32_t) * (kBlock / kWave);
-  hipLaunchKernelGGL((k_walk_persistent<ALGO, W, MULTI>), dim3(blocks), dim3(kBlock), lds,
-                     stream, g, rq, status, head, cfg);
+                     const TuneCfg& cfg, unsigned blocks, unsigned block, hipStream_t stream) {
+  const size_t lds = (size_t)cfg.hash_cells * sizeof(uint32_t) * (block / kWave) +
+                     (size_t)cfg.hub_buckets * kHubBucketWords * sizeof(uint32_t);
+  hipLaunchKernelGGL((k_walk_persistent<ALGO, W, MULTI>), dim3(blocks), dim3(block), lds, stream,
+                     g, rq, status, head, cfg);
   return hipGetLastError();
 }
 
 template <bool MULTI>
 static hipError_t launch_any(int algo, const DevGraph& g, const Reqs<MULTI>& rq, uint32_t* status,
-                             uint64_t* head, int num_cus, const TuneCfg& c, uint64_t n,
+                             uint64_t* head, int num_cus, const TuneCfg& tuned, uint64_t n,
                              hipStream_t stream) {
+  TuneCfg c = tuned;
   if (c.tiny_max > 16 || c.wgs_per_cu == 0 || c.hash_cells < 64 ||
       (c.hash_cells & (c.hash_cells - 1)) || head == nullptr)
     return hipErrorInvalidValue;
@@ -759,25 +784,41 @@ static hipError_t launch_any(int algo, const DevGraph& g, const Reqs<MULTI>& rq,
   // Unit weights: nothing to sum, a lane per query.
   if (!wt && (algo == kDeepWalk || algo == kPPR))
     return launch_uniform<MULTI>(algo, g, rq, status, head, num_cus, c.wgs_per_cu, n, stream);
-  uint64_t blocks = (uint64_t)num_cus * c.wgs_per_cu;
-  const uint64_t per_block = (kBlock / kWave) * kGroups;
-  const uint64_t need = (n + per_block - 1) / per_block;
-  if (blocks > need) blocks = need;
-  if (blocks == 0) blocks = 1;
+  if (algo != kNode2Vec) c.hash_cells = 0;  // only node2vec uses the regions
+  // Wavefronts: enough for four queries each, at most wgs_per_cu times four
+  // per CU.  Where they fill the chip they run in workgroups as large as the
+  // configuration divides into, which share one hub cache in what the
+  // regions leave of their part of the LDS; a smaller launch spreads over the
+  // CUs in workgroups of four wavefronts.
+  const uint64_t full = (uint64_t)num_cus * c.wgs_per_cu * 4;
+  const uint64_t waves = std::min((n + kGroups - 1) / kGroups, full);
+  uint32_t block = 256;
+  size_t budget = 0;
+  for (uint32_t b : {1024u, 512u, 256u}) {
+    const uint32_t per = b / 256;
+    if (c.wgs_per_cu % per || (b > 256 && waves < full)) continue;
+    budget = kCuLds / (c.wgs_per_cu / per) / kLdsGrain * kLdsGrain;
+    block = b;
+    if ((size_t)c.hash_cells * sizeof(uint32_t) * (b / kWave) <= budget) break;
+  }
+  const size_t regions = (size_t)c.hash_cells * sizeof(uint32_t) * (block / kWave);
+  constexpr size_t kBucketBytes = kHubBucketWords * sizeof(uint32_t);
+  c.hub_buckets = regions < budget ? (uint32_t)((budget - regions) / kBucketBytes) : 0;
+  const uint64_t per_block = block / kWave;
+  const unsigned b = (unsigned)std::max<uint64_t>(1, (waves + per_block - 1) / per_block);
   const hipError_t e = reset_counter(head, stream);
   if (e != hipSuccess) return e;
-  const unsigned b = (unsigned)blocks;
   switch (algo) {
     case kDeepWalk:
-      return go<kDeepWalk, true>(g, rq, status, head, c, b, stream);
+      return go<kDeepWalk, true>(g, rq, status, head, c, b, block, stream);
     case kNode2Vec:
-      return wt ? go<kNode2Vec, true>(g, rq, status, head, c, b, stream)
-                : go<kNode2Vec, false>(g, rq, status, head, c, b, stream);
+      return wt ? go<kNode2Vec, true>(g, rq, status, head, c, b, block, stream)
+                : go<kNode2Vec, false>(g, rq, status, head, c, b, block, stream);
     case kMetaPath:
-      return wt ? go<kMetaPath, true>(g, rq, status, head, c, b, stream)
-                : go<kMetaPath, false>(g, rq, status, head, c, b, stream);
+      return wt ? go<kMetaPath, true>(g, rq, status, head, c, b, block, stream)
+                : go<kMetaPath, false>(g, rq, status, head, c, b, block, stream);
     case kPPR:
-      return go<kPPR, true>(g, rq, status, head, c, b, stream);
+      return go<kPPR, true>(g, rq, status, head, c, b, block, stream);
     default:
       return hipErrorInvalidValue;
   }

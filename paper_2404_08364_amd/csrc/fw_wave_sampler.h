@@ -24,6 +24,7 @@
 #pragma once
 
 #include "fw_device.h"
+#include "fw_hub_cache.h"
 
 namespace fw {
 
@@ -261,15 +262,20 @@ __device__ __forceinline__ int64_t pick_in_quads(const uint64_t w[4], const Quad
 // Descends from quads [lo, lo + len) to the picked entry.  With have_r the
 // draw r (below the range's total) is given; otherwise the first level's
 // total T yields r = floor(u * T / 2^64).  Returns the index relative to s.o,
-// or -1 when the total is 0.  ev is bound.
-template <class E>
+// or -1 when the total is 0.  ev is bound.  The totals of the first level of a
+// whole row (have_r not set) may come from `hubs`.
+template <class E, class H>
 __device__ __forceinline__ int64_t wave_descend(const E& ev, const QuadSlice& s, uint32_t lo,
                                                 uint32_t len, uint64_t r, bool have_r,
-                                                uint64_t u) {
+                                                uint64_t u, const H& hubs) {
   const int lane = lane_id();
   while (len > (uint32_t)kWave) {
     const GroupSplit sp(len);
-    const uint64_t mine = wave_group_totals(ev, s, lo, len, sp);
+    uint64_t mine;
+    if (have_r || !hubs.find(s.d, mine)) {
+      mine = wave_group_totals(ev, s, lo, len, sp);
+      if (!have_r) hubs.keep(s.d, mine);
+    }
     const uint64_t incl = wave_incl_scan(mine);
     if (!have_r) {
       const uint64_t total = readlane64(incl, kWave - 1);
@@ -294,15 +300,16 @@ __device__ __forceinline__ int64_t wave_descend(const E& ev, const QuadSlice& s,
 template <class E>
 __device__ __forceinline__ uint64_t wave_locate(const E& ev, const QuadSlice& s, uint32_t lo,
                                                 uint32_t len, uint64_t r) {
-  return (uint64_t)wave_descend(bind_quads(ev, s), s, lo, len, r, true, 0);
+  return (uint64_t)wave_descend(bind_quads(ev, s), s, lo, len, r, true, 0, NoHubs{});
 }
 
 // Returns the index (relative to the slice) of the picked neighbour, or -1
 // when the slice's total weight is 0.  o, d and u are wave-uniform.
-template <class E>
-__device__ __forceinline__ int64_t wave_pick(const E& ev, uint64_t o, uint64_t d, uint64_t u) {
+template <class E, class H = NoHubs>
+__device__ __forceinline__ int64_t wave_pick(const E& ev, uint64_t o, uint64_t d, uint64_t u,
+                                             const H& hubs = H{}) {
   const QuadSlice s(o, d);
-  return wave_descend(bind_quads(ev, s), s, 0, s.nq, 0, false, u);
+  return wave_descend(bind_quads(ev, s), s, 0, s.nq, 0, false, u, hubs);
 }
 
 }  // namespace fw
