@@ -547,11 +547,22 @@ k_walk_persistent(
   }
 
   // This group's query (identical in the 16 lanes of the group): request r,
-  // index in the request, vertex state.
-  uint64_t s_qid = 0, s_o = 0, s_d = 0;
+  // index in the request, vertex state, row range of the current and (node2vec)
+  // of the previous vertex.
+  uint64_t s_qid = 0, s_o = 0, s_po = 0;
+  uint32_t s_d = 0, s_pd = 0;
   uint32_t s_cur = kEnd, s_prev = kEnd, s_t = 0, s_r = 0;
   bool s_live = false;
   bool exhausted = false;
+  // Draws of 16 hops at a time: lane j of a group holds the one of hop
+  // s_t - s_t mod 16 + j, and its bit of `stops` PPR's coin for that hop.  A
+  // Philox block is 80 32-bit multiply-adds below the full VALU rate, too many
+  // for every hop on the whole wavefront.  With the picked ids of the four
+  // queries read by one load per round (they were read hop by hop) and
+  // N(prev)'s bounds kept from the last hop: 524,288 weighted DeepWalk walks of
+  // 80 hops on R-MAT-22 35.8 and 27.9 ms before and after, node2vec 137.9 and
+  // 132.5 ms, 2,097,152 MetaPath walks on Chung-Lu 2^22 27.3 and 24.6 ms.
+  uint64_t s_u = 0, stops = 0;
 
   for (;;) {
     // ---- refill: claim one query for every empty group ----------------
@@ -582,6 +593,7 @@ k_walk_persistent(
                 s_cur = st;
                 s_prev = kEnd;
                 s_t = 0;
+                s_d = 0;
                 s_live = true;
               }
             }
@@ -596,60 +608,50 @@ k_walk_persistent(
       continue;
     }
     if (s_live) {
+      if (ALGO == kNode2Vec) {
+        s_po = s_o;  // the last hop's row is N(prev) of this one
+        s_pd = s_d;
+      }
       s_o = g.off[s_cur];
-      s_d = g.off[s_cur + 1] - s_o;
-      // A PPR stop ends the query like a dead end: the tiny path pads it.
+      s_d = (uint32_t)(g.off[(uint64_t)s_cur + 1] - s_o);
+    }
+    const bool fresh = s_live && s_t % kGroupLanes == 0;
+    const uint64_t fresh_m = ballot(fresh);
+    if (fresh_m) {
+      const ReqDesc R = rq.get(s_r);
+      uint64_t word1;
+      const uint64_t u = philox_draw2(R.seed, R.qid_base + s_qid, s_t + (uint64_t)gl, word1);
+      if (fresh) s_u = u;
       if (ALGO == kPPR) {
-        const ReqDesc R = rq.get(s_r);
-        if (ppr_stops(R.prm, R.seed, R.qid_base + s_qid, s_t)) s_d = 0;
+        const bool stop = __umul64hi(word1, (uint64_t)R.prm.stop_den) < (uint64_t)R.prm.stop_num;
+        stops = (stops & ~fresh_m) | (ballot(stop) & fresh_m);
       }
     }
+    const int hop_lane = grp * kGroupLanes + (int)(s_t % kGroupLanes);  // holds the hop's draw
+    // A PPR stop ends the query like a dead end: the tiny path finds no weight.
+    if (ALGO == kPPR && s_live && ((stops >> hop_lane) & 1u)) s_d = 0;
+    int32_t s_idx = -1;  // the hop's pick, -1: the walk ends
 
     // ---- tiny hops: one per 16-lane group ------------------------------
     const bool tiny = s_live && s_d <= cfg.tiny_max;
-    if (ballot(tiny)) {
-      const ReqDesc R = rq.get(tiny ? s_r : 0);
-      const DevParams& prm = R.prm;
-      const uint32_t length = R.length;
-      const uint64_t row_len = (uint64_t)length + 1;
+    if (ballot(tiny && s_d != 0)) {
+      const DevParams prm = rq.get(tiny ? s_r : 0).prm;
       auto ev = base_eval<ALGO, WEIGHTED, MemberGlobal>(g, prm, tiny ? s_o : 0,
                                                         tiny ? s_prev : kEnd, tiny ? s_t : 0);
       ev.mem.adj = g.adj;
-      ev.mem.po = 0;
-      ev.mem.pd = 0;
-      if (ALGO == kNode2Vec && tiny && s_t > 0) {
-        ev.mem.po = g.off[s_prev];
-        ev.mem.pd = g.off[s_prev + 1] - ev.mem.po;
-      }
-      const bool valid = tiny && (uint64_t)gl < s_d;
+      ev.mem.po = s_po;
+      ev.mem.pd = tiny && s_t > 0 ? s_pd : 0;
+      const bool valid = tiny && (uint32_t)gl < s_d;
       uint64_t x = valid ? ev(gl) : 0ull;
       x += dpp64<0x111, 0xF>(x);  // inclusive scan inside each 16-lane row
       x += dpp64<0x112, 0xF>(x);
       x += dpp64<0x114, 0xF>(x);
       x += dpp64<0x118, 0xF>(x);
       const uint64_t total = shfl64(x, lane | 15);
-      const uint64_t u = philox_draw(R.seed, R.qid_base + s_qid, s_t);
-      const uint64_t r = scale_draw(u, total);
+      const uint64_t r = scale_draw(shfl64(s_u, hop_lane), total);
       const uint64_t m = ballot(valid && x > r);
       const uint32_t gm = (uint32_t)(m >> (grp * kGroupLanes)) & 0xFFFFu;
-      if (tiny) {
-        uint32_t* row = R.out + s_qid * row_len;
-        if (total == 0) {
-          for (uint32_t p = s_t + 1 + gl; p <= length; p += kGroupLanes) row[p] = kEnd;
-          s_live = false;
-          if (MULTI && gl == 0) count_steps(R, s_t);
-        } else {
-          const uint32_t next = g.adj[s_o + (gm ? __builtin_ctz(gm) : 0)];
-          if (gl == 0) row[s_t + 1] = next;
-          s_prev = s_cur;
-          s_cur = next;
-          s_t += 1;
-          if (s_t == length) {
-            s_live = false;
-            if (MULTI && gl == 0) count_steps(R, length);
-          }
-        }
-      }
+      if (tiny && total != 0) s_idx = gm ? __builtin_ctz(gm) : 0;
     }
 
     // ---- other hops: one at a time on the whole wavefront --------------
@@ -657,18 +659,15 @@ k_walk_persistent(
     while (big) {
       const int src = first_lane(big);
       big &= big - 1;
-      const uint64_t qid = readlane64(s_qid, src), o = readlane64(s_o, src),
-                     d = readlane64(s_d, src);
+      const uint64_t o = readlane64(s_o, src), d = readlane32(s_d, src);
       const uint32_t t = readlane32(s_t, src), prev = readlane32(s_prev, src);
-      const ReqDesc R = rq.get(readlane32(s_r, src));
-      const DevParams& prm = R.prm;
-      const uint32_t length = R.length;
+      const uint64_t u = readlane64(s_u, src + (int)(t % kGroupLanes));
+      const DevParams prm = rq.get(readlane32(s_r, src)).prm;
       tb.kind = 0;
       tb.po = tb.pd = 0;
       if (ALGO == kNode2Vec && t > 0) {
-        // Wave-uniform: kept in scalar registers.
-        tb.po = uniform64(g.off[prev]);
-        tb.pd = uniform64(g.off[prev + 1]) - tb.po;
+        tb.po = readlane64(s_po, src);
+        tb.pd = readlane32(s_pd, src);
         // N(prev) much shorter than N(cur): look its keys up in N(cur)
         // instead of testing every entry of N(cur) against it.
         if (cfg.sparse_ratio != 0 && d >= kSparseMinDegree && tb.cells >= 2 * kWave &&
@@ -677,7 +676,6 @@ k_walk_persistent(
         else
           build_table(tb, g.adj, d, lane);
       }
-      const uint64_t u = philox_draw(R.seed, R.qid_base + qid, t);
       auto ev = base_eval<ALGO, WEIGHTED, MemberAny>(g, prm, o, prev, t);
       ev.narrow = cfg.narrow != 0;
       hubs.cur = readlane32(s_cur, src);
@@ -733,24 +731,25 @@ k_walk_persistent(
       } else {
         idx = wave_pick(ev, o, d, u, hubs);
       }
-      uint32_t* row = R.out + qid * ((uint64_t)length + 1);
-      const bool mine = grp == src / kGroupLanes;
-      if (idx < 0) {
-        for (uint32_t p = t + 1 + lane; p <= length; p += kWave) row[p] = kEnd;
-        if (mine) s_live = false;
-        if (MULTI && lane == src) count_steps(R, t);
-      } else {
-        const uint32_t next = g.adj[o + (uint64_t)idx];
-        if (lane == 0) row[t + 1] = next;
-        if (mine) {
-          s_prev = s_cur;
-          s_cur = next;
-          s_t += 1;
-          if (s_t == length) s_live = false;
-        }
-        if (MULTI && lane == src && t + 1 == length) count_steps(R, length);
-      }
+      if (grp == src / kGroupLanes) s_idx = (int32_t)idx;
       wave_sync_lds();
+    }
+
+    // ---- all hops: read the picked ids, emit, advance or end -------------
+    if (s_live) {
+      const ReqDesc R = rq.get(s_r);
+      uint32_t* row = R.out + s_qid * ((uint64_t)R.length + 1);
+      if (s_idx < 0) {
+        for (uint64_t p = (uint64_t)s_t + 1 + gl; p <= R.length; p += kGroupLanes) row[p] = kEnd;
+        s_live = false;
+      } else {
+        s_prev = s_cur;
+        s_cur = g.adj[s_o + (uint32_t)s_idx];
+        s_t += 1;
+        if (gl == 0) row[s_t] = s_cur;
+        s_live = s_t != R.length;
+      }
+      if (MULTI && !s_live && gl == 0) count_steps(R, s_t);
     }
   }
 }
