@@ -46,6 +46,10 @@ __device__ __forceinline__ uint32_t bucket_of(uint32_t u, uint32_t shift) {
   return (uint32_t)__umul24(u, kFib24) >> shift;
 }
 constexpr int kGroups = 4;  // queries per wavefront
+// Queries claimed at a time, at most.  1,048,576 PPR walks from the hub of
+// R-MAT-22 took 10.3 ms with one atomic per round that emptied a group, 6.2 ms
+// with claims of up to 32 that shrink towards the end.
+constexpr uint64_t kMaxClaim = 32;
 // Node2vec hops from vertices of at least this degree may take the
 // sparse-N(prev) pass (sparse_prev_group_totals).
 constexpr uint64_t kSparseMinDegree = 2048;
@@ -553,7 +557,15 @@ k_walk_persistent(
   uint32_t s_d = 0, s_pd = 0;
   uint32_t s_cur = kEnd, s_prev = kEnd, s_t = 0, s_r = 0;
   bool s_live = false;
-  bool exhausted = false;
+  // Queries this wavefront may start: its first ones by its index, the others
+  // claimed from the head counter, which counts the queries past the
+  // wavefronts' first ones.
+  const uint32_t waves = gridDim.x * (blockDim.x / kWave);
+  uint64_t pool = uniform64(((uint64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave) *
+                            cfg.slots);
+  uint64_t pool_end = min(pool + cfg.slots, n);
+  pool = min(pool, n);
+  bool exhausted = pool == n;
   // Draws of 16 hops at a time: lane j of a group holds the one of hop
   // s_t - s_t mod 16 + j, and its bit of `stops` PPR's coin for that hop.  A
   // Philox block is 80 32-bit multiply-adds below the full VALU rate, too many
@@ -565,20 +577,33 @@ k_walk_persistent(
   uint64_t s_u = 0, stops = 0;
 
   for (;;) {
-    // ---- refill: claim one query for every empty group ----------------
+    // ---- refill: one query for every empty group -----------------------
     if (!exhausted) {
-      const uint64_t empty_m = ballot(!s_live && gl == 0);
+      const uint64_t empty_m = ballot(!s_live && gl == 0 && (uint32_t)grp < cfg.slots);
       const uint32_t empty = __builtin_popcountll(empty_m);
       if (empty) {
-        uint64_t base = 0;
-        if (lane == 0) base = atomicAdd((unsigned long long*)head, (unsigned long long)empty);
-        base = readlane64(base, 0);
-        if (base + empty >= n) exhausted = true;
-        if (!s_live) {
+        if (pool == pool_end) {
+          // Claim an eighth of this wavefront's share of what is left (at
+          // least one query per empty group): many short walks then cost few
+          // atomics on the one counter, and the last claims are small.
+          const uint64_t left = n - pool_end;
+          uint64_t k = left / ((uint64_t)waves * 8);
+          k = k < empty ? empty : k > kMaxClaim ? kMaxClaim : k;
+          uint64_t base = 0;
+          if (lane == 0) base = atomicAdd((unsigned long long*)head, (unsigned long long)k);
+          pool = waves * (uint64_t)cfg.slots + readlane64(base, 0);
+          pool_end = pool + k;
+          if (pool >= n) exhausted = true;
+          pool_end = pool_end < n ? pool_end : n;
+          pool = pool < n ? pool : n;
+        }
+        const uint64_t base = pool;
+        const uint64_t next = pool + empty;
+        if (!s_live && (uint32_t)grp < cfg.slots) {
           const uint32_t rank =
               __builtin_popcountll(empty_m & ((1ull << (grp * kGroupLanes)) - 1));
           const uint64_t q = base + rank;
-          if (q < n) {
+          if (q < pool_end) {
             const uint32_t r = rq.find(q);
             const ReqDesc R = rq.get(r);
             const uint64_t lq = q - rq.first(r);
@@ -599,8 +624,11 @@ k_walk_persistent(
             }
           }
           // An invalid or length-0 query leaves its group empty; the next
-          // round claims again.
+          // round refills it.
         }
+        pool = next < pool_end ? next : pool_end;
+        if (pool == pool_end && (pool_end == n || n <= waves * (uint64_t)cfg.slots))
+          exhausted = true;
       }
     }
     if (!ballot(s_live)) {
@@ -784,13 +812,17 @@ static hipError_t launch_any(int algo, const DevGraph& g, const Reqs<MULTI>& rq,
   if (!wt && (algo == kDeepWalk || algo == kPPR))
     return launch_uniform<MULTI>(algo, g, rq, status, head, num_cus, c.wgs_per_cu, n, stream);
   if (algo != kNode2Vec) c.hash_cells = 0;  // only node2vec uses the regions
-  // Wavefronts: enough for four queries each, at most wgs_per_cu times four
-  // per CU.  Where they fill the chip they run in workgroups as large as the
+  // Wavefronts: at most wgs_per_cu times four per CU, each with up to four
+  // queries, and one while there are wavefronts for all (a wavefront runs
+  // the long hops of its queries one after the other).  Where they fill the chip they run in workgroups as large as the
   // configuration divides into, which share one hub cache in what the
   // regions leave of their part of the LDS; a smaller launch spreads over the
-  // CUs in workgroups of four wavefronts.
+  // CUs in workgroups of four wavefronts.  3,001 node2vec walks of 80 hops on
+  // R-MAT-20: 6.59 ms with four queries to each of 751 wavefronts, 2.40 ms so.
   const uint64_t full = (uint64_t)num_cus * c.wgs_per_cu * 4;
-  const uint64_t waves = std::min((n + kGroups - 1) / kGroups, full);
+  c.slots = (uint32_t)std::min<uint64_t>(kGroups, (n + full - 1) / full);
+  if (c.slots == 0) c.slots = 1;
+  const uint64_t waves = std::min((n + c.slots - 1) / c.slots, full);
   uint32_t block = 256;
   size_t budget = 0;
   for (uint32_t b : {1024u, 512u, 256u}) {
@@ -805,8 +837,10 @@ static hipError_t launch_any(int algo, const DevGraph& g, const Reqs<MULTI>& rq,
   c.hub_buckets = regions < budget ? (uint32_t)((budget - regions) / kBucketBytes) : 0;
   const uint64_t per_block = block / kWave;
   const unsigned b = (unsigned)std::max<uint64_t>(1, (waves + per_block - 1) / per_block);
-  const hipError_t e = reset_counter(head, stream);
-  if (e != hipSuccess) return e;
+  if ((uint64_t)b * per_block * c.slots < n) {  // only then is the counter claimed from
+    const hipError_t e = reset_counter(head, stream);
+    if (e != hipSuccess) return e;
+  }
   switch (algo) {
     case kDeepWalk:
       return go<kDeepWalk, true>(g, rq, status, head, c, b, block, stream);
