@@ -60,7 +60,8 @@ def byte_model(algo: str, weighted: bool, labelled: bool):
 # Sources the persistent walker kernel is compiled from; its compiler flags
 # are hashed with them.
 WALKER_SOURCES = ["csrc/fw_device.h", "csrc/fw_wave_sampler.h", "csrc/fw_kernels.h",
-                  "csrc/fw_requests.h", "csrc/fw_hub_cache.h", "csrc/fw_uniform.hip",
+                  "csrc/fw_requests.h", "csrc/fw_hub_cache.h", "csrc/fw_member.h",
+                  "csrc/fw_uniform.hip", "csrc/fw_team.hip",
                   "csrc/fw_persistent.hip"]
 
 

@@ -142,6 +142,9 @@ int fw_walk(const fw_graph* g, fw_algo algo, const fw_params* params, const uint
  *                       each keeps four queries, batches tiny-degree hops
  *                       four to a wavefront and runs the others on the whole
  *                       wavefront (sampler organisation of section 5.1).
+ *                       Launches of few queries that pass no fw_tune take a
+ *                       workgroup per query instead; unweighted DeepWalk and
+ *                       PPR a lane per query.
  *   FW_MODE_AUTO        FW_MODE_PERSISTENT with the tuned configuration.
  *   FW_MODE_STAGED      the paper's two-stage block design on wave64:
  *                       persistent workgroups with an LDS task pool, wave

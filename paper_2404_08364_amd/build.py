@@ -13,7 +13,8 @@ PKG = Path(__file__).resolve().parent
 ROOT = PKG.parent
 CSRC = PKG / "csrc"
 LIB = PKG / "libflowwalk.so"
-SOURCES = ["fw_runtime.hip", "fw_plain.hip", "fw_persistent.hip", "fw_uniform.hip", "fw_staged.hip",
+SOURCES = ["fw_runtime.hip", "fw_plain.hip", "fw_persistent.hip", "fw_uniform.hip", "fw_team.hip",
+           "fw_staged.hip",
            "fw_persistent_host.hip", "fw_server.hip", "fw_reservoir.hip", "fw_batch.hip",
            "fw_tasks.hip", "fw_noalloc.hip"]
 ARCH = os.environ.get("FW_OFFLOAD_ARCH", "gfx950")

@@ -320,27 +320,35 @@ struct Eval {
     return ~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu);
   }
 
-  // Weights of quad q of the run at qa (the arrays are padded so that a
-  // quad never ends past the allocation), entries outside the slice
-  // included: the caller masks them.  The offset from the uniform base qa is
+  // What quad q of the run at qa reads (the arrays are padded so that a quad
+  // never ends past the allocation).  The offset from the uniform base qa is
   // 32-bit (slices are < 2^28 entries), so each load is one scalar base plus
   // one vector offset.
-  __device__ __forceinline__ void quad(uint32_t q, uint64_t out[4]) const {
-    uint32_t wq[4] = {1u, 1u, 1u, 1u};
-    if (WEIGHTED) {
-      const uint4 v = *reinterpret_cast<const uint4*>(
-          reinterpret_cast<const char*>(w + qa) + q * 16u);
-      wq[0] = v.x; wq[1] = v.y; wq[2] = v.z; wq[3] = v.w;
-    }
+  struct Loaded {
+    uint4 w, a;  // weights; node2vec past the first hop: ids
+    uint32_t l;  // MetaPath: labels, entry j in byte j
+  };
+  __device__ __forceinline__ uint4 quad_ids(uint32_t q) const {
+    return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(adj + qa) + q * 16u);
+  }
+  __device__ __forceinline__ Loaded load(uint32_t q) const {
+    Loaded v{make_uint4(1u, 1u, 1u, 1u), make_uint4(0u, 0u, 0u, 0u), 0u};
+    if (WEIGHTED) v.w = quad_raw(q);
+    if (ALGO == kNode2Vec && !first) v.a = quad_ids(q);
+    if (ALGO == kMetaPath) v.l = quad_labels(q);
+    return v;
+  }
+  // The quad's transition weights, entries outside the slice included: the
+  // caller masks them.
+  __device__ __forceinline__ void weights(const Loaded& v, uint64_t out[4]) const {
+    const uint32_t wq[4] = {v.w.x, v.w.y, v.w.z, v.w.w};
     if (ALGO == kNode2Vec) {
       if (first) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) out[j] = wq[j];
         return;
       }
-      const uint4 a = *reinterpret_cast<const uint4*>(
-          reinterpret_cast<const char*>(adj + qa) + q * 16u);
-      const uint32_t u[4] = {a.x, a.y, a.z, a.w};
+      const uint32_t u[4] = {v.a.x, v.a.y, v.a.z, v.a.w};
       // f_in for a neighbour of prev, f_out otherwise, then f_ret for prev.
       uint32_t f[4];
       mem.factors4(u, f_in, f_out, f);
@@ -356,14 +364,15 @@ struct Eval {
         for (int j = 0; j < 4; ++j) out[j] = (uint64_t)wq[j] * f[j];
       }
     } else if (ALGO == kMetaPath) {
-      const uint32_t l = *reinterpret_cast<const uint32_t*>(
-          reinterpret_cast<const char*>(lab + qa) + q * 4u);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) out[j] = (((l >> (8 * j)) & 0xFFu) == want) ? wq[j] : 0ull;
+      for (int j = 0; j < 4; ++j) out[j] = (((v.l >> (8 * j)) & 0xFFu) == want) ? wq[j] : 0ull;
     } else {
 #pragma unroll
       for (int j = 0; j < 4; ++j) out[j] = wq[j];
     }
+  }
+  __device__ __forceinline__ void quad(uint32_t q, uint64_t out[4]) const {
+    weights(load(q), out);
   }
 };
 

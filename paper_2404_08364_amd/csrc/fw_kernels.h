@@ -46,7 +46,9 @@ struct LaunchArgs {
   uint32_t* status;     // device: bit 0 set when a start vertex is >= V
   uint64_t* head;       // device: global task-pool head (persistent form)
   int num_cus;
+  uint64_t max_deg;
   TuneCfg cfg;
+  bool tuned_by_caller;  // run the persistent form as configured, also for few queries
 };
 
 // One walk request of a multi-request launch (the served form): query i of
@@ -79,6 +81,9 @@ hipError_t launch_persistent_multi(int algo, const DevGraph& g, const ReqTable& 
                                    uint32_t* status, uint64_t* head, int num_cus,
                                    const TuneCfg& cfg, hipStream_t stream);
 hipError_t launch_persistent(const LaunchArgs& a, hipStream_t stream);
+// Small launches of the persistent form: a workgroup per query (fw_team.hip).
+bool team_walks(const LaunchArgs& a);
+hipError_t launch_team(const LaunchArgs& a, hipStream_t stream);
 hipError_t launch_staged(const LaunchArgs& a, hipStream_t stream);
 
 }  // namespace fw

@@ -67,6 +67,7 @@ extern "C" int fw_walk_noalloc(const fw_graph* g, fw_algo algo, const fw_params*
   a.status = g->d_status;
   a.head = head;
   a.num_cus = g->num_cus;
+  a.max_deg = g->max_deg;
   bool staged = false;
   rc = fw::resolve_tune(g, (int)algo, FW_MODE_PERSISTENT, nullptr, &a.cfg, &staged);
   if (rc) return rc;

@@ -28,23 +28,12 @@
 
 #include "fw_hub_cache.h"
 #include "fw_kernels.h"
+#include "fw_member.h"
 #include "fw_requests.h"
 #include "fw_wave_sampler.h"
 
 namespace fw {
 
-extern __shared__ __attribute__((aligned(16))) uint32_t fw_dyn_lds[];
-
-constexpr uint32_t kFib24 = 0x9E3779u;  // 2^24 / golden ratio
-
-// Bucket of key u in a table of 2^(32 - shift) buckets (Fibonacci hashing:
-// the top bits of the low word of u times 2^24 / golden ratio).  The 24-bit
-// multiply runs at the full VALU rate (a 32-bit one at a quarter); ids from
-// 2^24 on hash by their low 24 bits, which costs probes, never exactness.
-// (HIP's __umul24 returns a signed int: go through uint32_t.)
-__device__ __forceinline__ uint32_t bucket_of(uint32_t u, uint32_t shift) {
-  return (uint32_t)__umul24(u, kFib24) >> shift;
-}
 constexpr int kGroups = 4;  // queries per wavefront
 // Queries claimed at a time, at most.  1,048,576 PPR walks from the hub of
 // R-MAT-22 took 10.3 ms with one atomic per round that emptied a group, 6.2 ms
@@ -65,95 +54,12 @@ constexpr int kMaxBlock = 1024;  // threads per workgroup
 constexpr size_t kCuLds = 160 * 1024;
 constexpr size_t kLdsGrain = 1280;  // LDS is handed out in these steps
 
-__device__ __forceinline__ uint32_t log2_ceil(uint64_t x) {
-  uint32_t b = 0;
-  while ((1ull << b) < x) ++b;
-  return b;
-}
-
-// u is one of the four cells: the smallest XOR with u is 0.
-__device__ __forceinline__ bool has4(uint4 v, uint32_t u) {
-  return min(min(v.x ^ u, v.y ^ u), min(v.z ^ u, v.w ^ u)) == 0u;
-}
-
-// The bucket has a free cell.  Cells fill in order (an insert takes the first
-// free one), so that is the last cell being free.
-__device__ __forceinline__ bool open4(uint4 v) { return v.w == kEnd; }
-
-// Membership in N(prev) for one node2vec hop, by a wave-uniform mode:
-//   0  binary search of the sorted row in global memory;
-//   1  exact hash set in LDS: nb buckets of 4 cells (16 bytes) at
-//      fw_dyn_lds[base, base + 4 nb), kEnd marks an empty cell; a key lives
-//      in the first bucket, in probe order from its hash, that had a free cell
-//      when it was inserted, so a lookup stops at a hit or at a bucket with a
-//      free cell.
-// (Mode 2, the merge of sorted rows, has its own code: merge_chunk.)
-// One type for all modes keeps a single copy of the sampler in the kernel.
-struct MemberAny {
-  int mode;
-  uint32_t base, bmask, shift;
-  const uint32_t* __restrict__ adj;
-  uint64_t po, pd;
-
-  // base is a multiple of 4 cells, so a bucket is one aligned 16-byte read.
-  __device__ __forceinline__ uint4 bucket(uint32_t b) const {
-    return reinterpret_cast<const uint4*>(fw_dyn_lds)[(base >> 2) + b];
-  }
-  __device__ __forceinline__ bool probe_rest(uint32_t u, uint32_t b) const {
-    for (;;) {
-      b = (b + 1) & bmask;
-      const uint4 v = bucket(b);
-      if (has4(v, u)) return true;
-      if (open4(v)) return false;
-    }
-  }
-  // f[j] = fin if u[j] is in N(prev), else fout.  Choosing the factor inside
-  // the lookup keeps the hits in lane masks on the common path; only the
-  // rare longer probes update a factor under a lane mask.
-  __device__ __forceinline__ void factors4(const uint32_t u[4], uint32_t fin, uint32_t fout,
-                                           uint32_t f[4]) const {
-    if (mode == 1) {
-      uint32_t b[4];
-      uint4 v[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        b[j] = bucket_of(u[j], shift);
-        v[j] = bucket(b[j]);
-      }
-      bool more = false;
-      bool done[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const bool hit = has4(v[j], u[j]);
-        f[j] = hit ? fin : fout;
-        done[j] = hit | open4(v[j]);
-        more |= !done[j];
-      }
-      if (more) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (!done[j]) f[j] = probe_rest(u[j], b[j]) ? fin : fout;
-      }
-      return;
-    }
-    bool hit[4];
-    row_contains4(adj, po, pd, u, hit);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) f[j] = hit[j] ? fin : fout;
-  }
-};
-
 struct Table {
   uint32_t base, cells;   // this wavefront's LDS region
   uint32_t bmask, shift;  // geometry of the hash set
   int kind;               // 0: global search, 1: hash set, 2: merge of sorted rows
   uint64_t po, pd;        // N(prev)
 };
-
-__device__ __forceinline__ void wave_sync_lds() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 
 // Chooses (and for the hash set builds) the membership structure of N(prev)
 // for one node2vec hop from a vertex of degree d, with the wavefront's lanes.
@@ -178,17 +84,7 @@ __device__ __forceinline__ void build_table(Table& tb, const uint32_t* __restric
     reinterpret_cast<uint4*>(fw_dyn_lds + tb.base)[i] = empty;
   wave_sync_lds();
   for (uint64_t i = lane; i < tb.pd; i += kWave) {
-    const uint32_t u = adj[tb.po + i];
-    uint32_t b = bucket_of(u, tb.shift);
-    for (;;) {
-      uint32_t j = 0;
-      for (; j < 4; ++j) {
-        const uint32_t old = atomicCAS(&fw_dyn_lds[tb.base + 4 * b + j], kEnd, u);
-        if (old == kEnd || old == u) break;
-      }
-      if (j < 4) break;
-      b = (b + 1) & tb.bmask;
-    }
+    hash_insert(tb.base, tb.bmask, tb.shift, adj[tb.po + i]);
   }
   wave_sync_lds();
   tb.kind = 1;
@@ -496,32 +392,6 @@ __device__ __forceinline__ uint64_t sparse_prev_group_totals(const E& ev, const 
   const uint64_t mine = (uint64_t)ev.f_out * raw + (uint64_t)corr[lane];
   wave_sync_lds();
   return (uint32_t)lane < sp.groups ? mine : 0ull;
-}
-
-template <int ALGO, bool WEIGHTED, class MEM>
-__device__ __forceinline__ Eval<ALGO, WEIGHTED, MEM> base_eval(const DevGraph& g,
-                                                              const DevParams& prm, uint64_t o,
-                                                              uint32_t prev, uint32_t t) {
-  Eval<ALGO, WEIGHTED, MEM> ev;
-  ev.adj = g.adj;
-  ev.w = g.w;
-  ev.lab = g.lab;
-  ev.o = o;
-  ev.first = (t == 0);
-  ev.prev = prev;
-  ev.f_ret = prm.f_ret;
-  ev.f_in = prm.f_in;
-  ev.f_out = prm.f_out;
-  ev.want = (ALGO == kMetaPath) ? schema_label(prm, t) : 0u;
-  ev.qa = 0;
-  ev.narrow = false;
-  return ev;
-}
-
-__device__ __forceinline__ uint64_t shfl64(uint64_t v, int src) {
-  const int lo = __builtin_amdgcn_ds_bpermute(src << 2, (int)(uint32_t)v);
-  const int hi = __builtin_amdgcn_ds_bpermute(src << 2, (int)(uint32_t)(v >> 32));
-  return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
 }
 
 // Eight wavefronts per SIMD (64 VGPRs): the walk is bound by the latency of
@@ -859,6 +729,7 @@ static hipError_t launch_any(int algo, const DevGraph& g, const Reqs<MULTI>& rq,
 
 // Enqueues (reset head; persistent kernel) on `stream`.
 hipError_t launch_persistent(const LaunchArgs& a, hipStream_t stream) {
+  if (!a.tuned_by_caller && team_walks(a)) return launch_team(a, stream);
   Reqs<false> rq;
   rq.one.starts = a.starts;
   rq.one.out = a.out;

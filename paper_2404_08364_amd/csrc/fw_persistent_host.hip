@@ -19,6 +19,7 @@ constexpr size_t kPoolLdsBytes = 16 * 1024;
 struct GraphKey {
   int algo;
   int staged;
+  int tuned_by_caller;
   TuneCfg cfg;
   DevParams prm;
   const uint32_t* starts;
@@ -184,6 +185,7 @@ hipError_t launch_persistent_checked(const fw_graph* g, const LaunchArgs& a, hip
   std::memset(&key, 0, sizeof(key));
   key.algo = a.algo;
   key.staged = staged;
+  key.tuned_by_caller = a.tuned_by_caller;
   key.cfg = a.cfg;
   key.prm = a.prm;
   key.starts = a.starts;
@@ -245,6 +247,7 @@ static int time_config(const fw_graph* g, LaunchArgs a, const TuneCfg& cfg, bool
                        hipStream_t stream, hipEvent_t e0, hipEvent_t e1, float* ms) {
   a.cfg = cfg;
   a.cfg.narrow = narrow_products(g->max_w, a.prm);
+  a.tuned_by_caller = true;
   auto launch = [&]() { return staged ? launch_staged(a, stream) : launch_persistent(a, stream); };
   hipError_t e = launch();  // warm-up
   *ms = 1e30f;
@@ -285,6 +288,7 @@ int autotune(fw_graph* g, int algo, const DevParams& dp, const uint32_t* starts,
   a.status = g->d_status;
   a.head = g->d_head + kHeadStride * (g->launches.fetch_add(1) % kHeadSlots);
   a.num_cus = g->num_cus;
+  a.max_deg = g->max_deg;
   const uint64_t lds_cu = 160 * 1024;  // LDS of a compute unit
   // Persistent form.  Coordinate search: occupancy x membership-table size,
   // then the tiny threshold.  Configurations that do not fit the LDS are

@@ -287,7 +287,7 @@ int fw_walk_ex(const fw_graph* g, fw_algo algo, const fw_params* params,
   fw_walk_opts o{};
   if (opts) o = *opts;
   hipStream_t stream = (hipStream_t)o.stream;
-  fw::LaunchArgs a;
+  fw::LaunchArgs a{};
   a.algo = (int)algo;
   a.g = fw::dev_graph(g);
   a.prm = dp;
@@ -300,6 +300,7 @@ int fw_walk_ex(const fw_graph* g, fw_algo algo, const fw_params* params,
   a.status = g->d_status;
   a.head = g->d_head + fw::kHeadStride * (g->launches.fetch_add(1) % fw::kHeadSlots);
   a.num_cus = g->num_cus;
+  a.max_deg = g->max_deg;
   hipError_t e;
   if (o.sampler != FW_SAMPLER_ITS) {
     if (o.sampler != FW_SAMPLER_DPRS && o.sampler != FW_SAMPLER_ZPRS)
@@ -315,6 +316,7 @@ int fw_walk_ex(const fw_graph* g, fw_algo algo, const fw_params* params,
     rc = fw::resolve_tune(g, (int)algo, o.mode, o.tune, &a.cfg, &staged);
     if (rc) return rc;
     a.cfg.narrow = fw::narrow_products(g->max_w, dp);
+    a.tuned_by_caller = o.tune != nullptr;
     e = fw::launch_persistent_checked(g, a, stream, o.use_graph != 0, staged);
   } else {
     return fail(FW_EINVAL, "unknown mode");
