@@ -160,6 +160,9 @@ __device__ __forceinline__ uint32_t uniform32(uint32_t v) {
 }
 
 __device__ __forceinline__ uint64_t wave_sum(uint64_t x) { return readlane64(wave_incl_scan(x), 63); }
+__device__ __forceinline__ uint32_t wave_sum32(uint32_t x) {
+  return readlane32(wave_incl_scan32(x), 63);
+}
 
 __device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
@@ -269,6 +272,9 @@ struct Eval {
   // Weight times factor is exact as a 24-bit multiply (bound checked per
   // launch on the host).
   bool narrow = false;
+  // The total of every group of a row, and of its last level, fits in 32 bits
+  // (bound checked per launch on the host).
+  bool sum32 = false;
 
   __device__ __forceinline__ uint64_t operator()(uint64_t i) const {
     const uint64_t e = o + i;

@@ -18,6 +18,7 @@ struct TuneCfg {
   uint32_t hash_cells;  // LDS hash-set cells per workgroup (power of two)
   uint32_t narrow;      // set per launch: max weight * max factor < 2^24, so a
                         // weight times a factor is one 24-bit multiply
+  uint32_t sum32;       // set per launch: every group total fits in 32 bits
   uint32_t sparse_ratio;  // persistent node2vec: a hop with d(cur) >= ratio *
                           // d(prev) looks N(prev)'s keys up in N(cur) (0: never)
   uint32_t hub_buckets;   // set per launch: buckets of the workgroup's hub cache
@@ -31,6 +32,16 @@ inline uint32_t narrow_products(uint64_t max_w, const DevParams& p) {
   if (p.f_out > f) f = p.f_out;
   if (f == 0) f = 1;
   return (max_w < (1ull << 24) && f < (1ull << 24) && max_w * f < (1ull << 24)) ? 1u : 0u;
+}
+
+// max_w * max_f times the entries of a row's largest group (a 64th of the row
+// in whole 256-entry chunks; a last level has at most 256) stays below 2^32.
+inline uint32_t sums_in_32_bits(uint64_t max_w, uint64_t max_deg, const DevParams& p) {
+  uint64_t f = p.f_ret;
+  if (p.f_in > f) f = p.f_in;
+  if (p.f_out > f) f = p.f_out;
+  if (f == 0) f = 1;
+  return (unsigned __int128)max_w * f * (max_deg / 64 + 512) < ((unsigned __int128)1 << 32);
 }
 
 struct LaunchArgs {

@@ -134,6 +134,7 @@ __device__ __forceinline__ Eval<ALGO, WEIGHTED, MEM> base_eval(const DevGraph& g
   ev.want = (ALGO == kMetaPath) ? schema_label(prm, t) : 0u;
   ev.qa = 0;
   ev.narrow = false;
+  ev.sum32 = false;
   return ev;
 }
 

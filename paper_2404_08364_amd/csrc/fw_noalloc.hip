@@ -72,6 +72,7 @@ extern "C" int fw_walk_noalloc(const fw_graph* g, fw_algo algo, const fw_params*
   rc = fw::resolve_tune(g, (int)algo, FW_MODE_PERSISTENT, nullptr, &a.cfg, &staged);
   if (rc) return rc;
   a.cfg.narrow = fw::narrow_products(g->max_w, dp);
+  a.cfg.sum32 = fw::sums_in_32_bits(g->max_w, g->max_deg, dp);
   // The counter is reset by a one-thread kernel ahead of the walk (no memset
   // node when the caller captures the stream).
   const hipError_t e = fw::launch_persistent(a, static_cast<hipStream_t>(stream));

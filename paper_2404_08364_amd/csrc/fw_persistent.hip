@@ -287,7 +287,7 @@ __device__ __forceinline__ uint64_t merge_group_totals(const E& ev, const QuadSl
       merge_chunk(ev, s, tb, c0, ge, cursor, lane, w, t);
       acc += t;
     }
-    const uint64_t tot = wave_sum(acc);
+    const uint64_t tot = ev.sum32 ? wave_sum32((uint32_t)acc) : wave_sum(acc);
     if ((uint32_t)lane == g) mine = tot;
   }
   return mine;
@@ -328,25 +328,8 @@ __device__ __forceinline__ uint64_t sparse_prev_group_totals(const E& ev, const 
   uint64_t raw = 0;
   if (ev.w != nullptr && hubs.find(s.d, raw)) {
   } else if (ev.w != nullptr) {
-    for (uint32_t g = 0; g < sp.groups; ++g) {
-      const uint32_t gb = g * sp.gsz;
-      const uint32_t ge = min(gb + sp.gsz, s.nq);
-      uint64_t acc = 0;
-      uint32_t q = gb + lane;
-#pragma unroll 1
-      for (; q + 3 * kWave < ge; q += 4 * kWave) {
-        uint4 v[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = quad_raw(q + k * kWave);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc += raw_quad_sum(s, q + k * kWave, v[k]);
-      }
-#pragma unroll 1
-      for (; q < ge; q += kWave) acc += raw_quad_sum(s, q, quad_raw(q));
-      const uint64_t tot = wave_sum(acc);
-      if ((uint32_t)lane == g) raw = tot;
-    }
+    raw = ev.sum32 ? raw_group_totals<uint32_t>(quad_raw, s, 0, s.nq, sp)
+                   : raw_group_totals<uint64_t>(quad_raw, s, 0, s.nq, sp);
     hubs.keep(s.d, raw);
   } else if ((uint32_t)lane < sp.groups) {
     const uint32_t gb = (uint32_t)lane * sp.gsz;
@@ -576,6 +559,7 @@ k_walk_persistent(
       }
       auto ev = base_eval<ALGO, WEIGHTED, MemberAny>(g, prm, o, prev, t);
       ev.narrow = cfg.narrow != 0;
+      ev.sum32 = cfg.sum32 != 0;
       hubs.cur = readlane32(s_cur, src);
       hubs.want = ev.want;
       ev.mem.mode = tb.kind == 1 ? 1 : 0;
@@ -613,7 +597,7 @@ k_walk_persistent(
             uint64_t cur = readlane64(gcur, gs);
             uint64_t w[4], t;
             merge_chunk(ev, qs, tb, lo, lo + len, cur, lane, w, t);
-            idx = pick_in_quads(w, qs, lo, len, r, true, 0);
+            idx = pick_in_quads(w, qs, lo, len, r, true, 0, ev.sum32);
           } else {
             if (sparse) {
               build_table(tb, g.adj, d, lane, false);

@@ -247,6 +247,7 @@ static int time_config(const fw_graph* g, LaunchArgs a, const TuneCfg& cfg, bool
                        hipStream_t stream, hipEvent_t e0, hipEvent_t e1, float* ms) {
   a.cfg = cfg;
   a.cfg.narrow = narrow_products(g->max_w, a.prm);
+  a.cfg.sum32 = sums_in_32_bits(g->max_w, g->max_deg, a.prm);
   a.tuned_by_caller = true;
   auto launch = [&]() { return staged ? launch_staged(a, stream) : launch_persistent(a, stream); };
   hipError_t e = launch();  // warm-up

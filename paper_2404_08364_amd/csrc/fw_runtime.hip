@@ -316,6 +316,7 @@ int fw_walk_ex(const fw_graph* g, fw_algo algo, const fw_params* params,
     rc = fw::resolve_tune(g, (int)algo, o.mode, o.tune, &a.cfg, &staged);
     if (rc) return rc;
     a.cfg.narrow = fw::narrow_products(g->max_w, dp);
+    a.cfg.sum32 = fw::sums_in_32_bits(g->max_w, g->max_deg, dp);
     a.tuned_by_caller = o.tune != nullptr;
     e = fw::launch_persistent_checked(g, a, stream, o.use_graph != 0, staged);
   } else {

@@ -234,9 +234,11 @@ hipError_t launch_batch(fw_server* s, Batch& b) {
                                      : std::max<uint32_t>(1, (cfg.wgs_per_cu - kExpressWgs) / bulk);
         cfg.wgs_per_cu = std::min(cfg.wgs_per_cu, w);
       }
-      cfg.narrow = 1;
-      for (uint32_t i = 0; i < k; ++i)
+      cfg.narrow = cfg.sum32 = 1;
+      for (uint32_t i = 0; i < k; ++i) {
         cfg.narrow &= fw::narrow_products(s->g->max_w, b.h_desc[ta][i].prm);
+        cfg.sum32 &= fw::sums_in_32_bits(s->g->max_w, s->g->max_deg, b.h_desc[ta][i].prm);
+      }
       // The phases of one algorithm run one after the other on this stream
       // and share its head counter.
       e = fw::launch_persistent_multi(a, dg, t, s->d_status, b.d_head + 16 * a, s->g->num_cus,

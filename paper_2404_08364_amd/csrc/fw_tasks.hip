@@ -32,6 +32,7 @@ struct TaskEval {
   __device__ __forceinline__ uint64_t operator()(uint64_t i) const { return w[o + i]; }
   static constexpr bool kCheapTotal = false;
   static constexpr bool kRawWeights = false;
+  static constexpr bool sum32 = false;
   __device__ __forceinline__ uint64_t quad_total4(uint32_t q) const {
     uint64_t o[4];
     quad(q, o);

@@ -87,7 +87,7 @@ __device__ __forceinline__ void team_totals(const E& ev, const QuadSlice& s, con
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const uint64_t tot = wave_sum(acc[k]);
+      const uint64_t tot = ev.sum32 ? wave_sum32((uint32_t)acc[k]) : wave_sum(acc[k]);
       if (lane == 0 && g0 + k * waves < sp.groups) totals[g0 + k * waves] = tot;
     }
   }
@@ -97,7 +97,7 @@ template <int ALGO, bool WEIGHTED>
 __global__ __launch_bounds__(kMaxWaves * kWave) void k_walk_team(
     DevGraph g, DevParams prm, const uint32_t* __restrict__ starts, uint32_t length,
     uint64_t seed, uint64_t qid_base, uint32_t* __restrict__ out, uint32_t* __restrict__ status,
-    uint32_t cells, uint32_t narrow) {
+    uint32_t cells, uint32_t narrow, uint32_t sum32) {
   __shared__ Job job;
   // After the hash set: the group totals of a long hop.
   uint64_t* totals = reinterpret_cast<uint64_t*>(fw_dyn_lds + cells);
@@ -125,6 +125,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_walk_team(
                        uint32_t m, uint32_t mask, uint32_t sh) {
     auto ev = base_eval<ALGO, WEIGHTED, MemberAny>(g, prm, row_o, p, hop);
     ev.narrow = narrow != 0;
+    ev.sum32 = sum32 != 0;
     ev.mem.mode = (int)m;
     ev.mem.base = 0;
     ev.mem.bmask = mask;
@@ -260,7 +261,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_walk_team(
             }
           }
           const uint64_t u = readlane64(draws, (int)(t % kWave));
-          const int64_t idx = pick_in_quads(w, s, lo, len, r, have_r, u);
+          const int64_t idx = pick_in_quads(w, s, lo, len, r, have_r, u, ev.sum32);
           if (idx >= 0) {
             const uint32_t e = (uint32_t)idx + s.lead;
             next = readlane32(component(ids, e & 3u), (int)(e / 4 - lo));
@@ -313,7 +314,7 @@ hipError_t go(const LaunchArgs& a, unsigned block, hipStream_t stream) {
   const uint32_t cells = ALGO == kNode2Vec ? kCellsPerThread * block : 0;
   hipLaunchKernelGGL((k_walk_team<ALGO, WEIGHTED>), dim3((unsigned)a.n), dim3(block),
                      cells * sizeof(uint32_t) + block * sizeof(uint64_t), stream, a.g, a.prm, a.starts, a.length, a.seed,
-                     a.qid_base, a.out, a.status, cells, a.cfg.narrow);
+                     a.qid_base, a.out, a.status, cells, a.cfg.narrow, a.cfg.sum32);
   return hipGetLastError();
 }
 
