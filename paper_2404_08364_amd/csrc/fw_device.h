@@ -38,6 +38,28 @@ struct DevParams {
 // same block is PPR's stop coin; the reservoir samplers draw entry i's word
 // from the block at (qid, t, i / 4, 1).
 // ---------------------------------------------------------------------------
+// 128-bit product m * c from four 32 x 32 + 64-bit multiply-adds (taken as
+// separate high and low products the compiler multiplies twice).
+__device__ __forceinline__ void mul_wide(uint64_t m, uint64_t c, uint64_t& hi, uint64_t& lo) {
+  const uint32_t ml = (uint32_t)m, mh = (uint32_t)(m >> 32);
+  const uint32_t cl = (uint32_t)c, ch = (uint32_t)(c >> 32);
+  const uint64_t p0 = (uint64_t)ml * cl;
+  const uint64_t p1 = (uint64_t)mh * cl + (p0 >> 32);
+  const uint64_t p2 = (uint64_t)ml * ch + (uint32_t)p1;
+  hi = (uint64_t)mh * ch + (p1 >> 32) + (p2 >> 32);
+  lo = (p2 << 32) | (uint32_t)p0;
+}
+
+// a ^ b ^ c, one instruction per 32 bits.
+__device__ __forceinline__ uint64_t xor3(uint64_t a, uint64_t b, uint64_t c) {
+  const uint32_t lo = __builtin_amdgcn_bitop3_b32((uint32_t)a, (uint32_t)b, (uint32_t)c, 0x96);
+  const uint32_t hi = __builtin_amdgcn_bitop3_b32((uint32_t)(a >> 32), (uint32_t)(b >> 32),
+                                                  (uint32_t)(c >> 32), 0x96);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// 217 VALU instructions per block with a uniform query id and hop (300 with
+// the products taken apart and two xors each).
 __device__ __forceinline__ void philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2, uint64_t c3,
                                               uint64_t seed, uint64_t out[4]) {
   constexpr uint64_t kM0 = 0xD2E7470EE14C6C93ull, kM1 = 0xCA5A826395121157ull;
@@ -45,11 +67,13 @@ __device__ __forceinline__ void philox4x64_10(uint64_t c0, uint64_t c1, uint64_t
   uint64_t k0 = seed, k1 = 0;
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    const uint64_t h0 = __umul64hi(kM0, c0), l0 = kM0 * c0;
-    const uint64_t h1 = __umul64hi(kM1, c2), l1 = kM1 * c2;
-    c0 = h1 ^ c1 ^ k0;
+    uint64_t h0, l0, h1, l1;
+    mul_wide(kM0, c0, h0, l0);
+    mul_wide(kM1, c2, h1, l1);
+    // The first rounds of a uniform counter word stay on the scalar unit.
+    c0 = r < 2 ? h1 ^ c1 ^ k0 : xor3(h1, c1, k0);
+    c2 = r < 2 ? h0 ^ c3 ^ k1 : xor3(h0, c3, k1);
     c1 = l1;
-    c2 = h0 ^ c3 ^ k1;
     c3 = l0;
     k0 += kW0;
     k1 += kW1;

@@ -35,10 +35,6 @@
 namespace fw {
 
 constexpr int kGroups = 4;  // queries per wavefront
-// Queries claimed at a time, at most.  1,048,576 PPR walks from the hub of
-// R-MAT-22 took 10.3 ms with one atomic per round that emptied a group, 6.2 ms
-// with claims of up to 32 that shrink towards the end.
-constexpr uint64_t kMaxClaim = 32;
 // Node2vec hops from vertices of at least this degree may take the
 // sparse-N(prev) pass (sparse_prev_group_totals).
 constexpr uint64_t kSparseMinDegree = 2048;

@@ -5,6 +5,11 @@
 
 namespace fw {
 
+// Queries claimed at a time, at most.  1,048,576 PPR walks from the hub of
+// R-MAT-22 took 10.3 ms with one atomic per round that emptied a group, 6.2 ms
+// with claims of up to 32 that shrink towards the end.
+constexpr uint64_t kMaxClaim = 32;
+
 // Request access: a single request passed by value, or a table of requests
 // (binary search of the query-count prefix maps a global index to its
 // request).
