@@ -44,11 +44,15 @@ constexpr uint64_t kSparseMinDegree = 2048;
 // N(prev) goes to the hash set or the merge.  Full passes on one MI355X for
 // ratios 16, 32, 64 and 128: R-MAT-22 node2vec 1308, 1272, 1275 and
 // 1330 ms; Chung-Lu 227M node2vec, 1M queries, 7157, 7084, 7021 and 6992 ms.
-constexpr uint64_t kSearchRatio = 64;
+// With the hubs' totals kept, ratios 16, 32 and 64: 524,288 walks on R-MAT-22
+// 133.8, 128.0 and 128.6 ms, 200,003 unweighted walks of 40 hops on Chung-Lu
+// 2^20, whose rows stay in the last-level cache, 17.7, 17.7 and 18.4 ms.
+constexpr uint64_t kSearchRatio = 32;
 constexpr int kGroupLanes = 16;
 constexpr int kMaxBlock = 1024;  // threads per workgroup
 constexpr size_t kCuLds = 160 * 1024;
 constexpr size_t kLdsGrain = 1280;  // LDS is handed out in these steps
+constexpr uint32_t kMaxRoomyCells = 4096;
 
 struct Table {
   uint32_t base, cells;   // this wavefront's LDS region
@@ -651,8 +655,8 @@ static hipError_t go(const DevGraph& g, const Reqs<MULTI>& rq, uint32_t* status,
 
 template <bool MULTI>
 static hipError_t launch_any(int algo, const DevGraph& g, const Reqs<MULTI>& rq, uint32_t* status,
-                             uint64_t* head, int num_cus, const TuneCfg& tuned, uint64_t n,
-                             hipStream_t stream) {
+                             uint64_t* head, int num_cus, const TuneCfg& tuned, bool roomy,
+                             uint64_t n, hipStream_t stream) {
   TuneCfg c = tuned;
   if (c.tiny_max > 16 || c.wgs_per_cu == 0 || c.hash_cells < 64 ||
       (c.hash_cells & (c.hash_cells - 1)) || head == nullptr)
@@ -662,6 +666,15 @@ static hipError_t launch_any(int algo, const DevGraph& g, const Reqs<MULTI>& rq,
   if (!wt && (algo == kDeepWalk || algo == kPPR))
     return launch_uniform<MULTI>(algo, g, rq, status, head, num_cus, c.wgs_per_cu, n, stream);
   if (algo != kNode2Vec) c.hash_cells = 0;  // only node2vec uses the regions
+  if (roomy && algo == kNode2Vec) {
+    // Fewer wavefronts than the configuration is for: larger regions, so that
+    // more rows go to the hash set instead of the merge (4,096 walks of 40 hops
+    // on R-MAT-20: 1.27 ms with 1,024 cells each, 1.16 ms with 2,048).
+    const uint64_t waves_per_cu = (n + num_cus - 1) / num_cus;
+    while (c.hash_cells < kMaxRoomyCells &&
+           2 * c.hash_cells * sizeof(uint32_t) * (waves_per_cu + 4) <= kCuLds)
+      c.hash_cells *= 2;
+  }
   // Wavefronts: at most wgs_per_cu times four per CU, each with up to four
   // queries, and one while there are wavefronts for all (a wavefront runs
   // the long hops of its queries one after the other).  Where they fill the chip they run in workgroups as large as the
@@ -721,7 +734,8 @@ hipError_t launch_persistent(const LaunchArgs& a, hipStream_t stream) {
   rq.one.pad = 0;
   rq.one.prm = a.prm;
   rq.tab = ReqTable{nullptr, nullptr, 0, 0};
-  return launch_any<false>(a.algo, a.g, rq, a.status, a.head, a.num_cus, a.cfg, a.n, stream);
+  return launch_any<false>(a.algo, a.g, rq, a.status, a.head, a.num_cus, a.cfg,
+                           !a.tuned_by_caller, a.n, stream);
 }
 
 hipError_t launch_persistent_multi(int algo, const DevGraph& g, const ReqTable& t,
@@ -730,7 +744,7 @@ hipError_t launch_persistent_multi(int algo, const DevGraph& g, const ReqTable& 
   Reqs<true> rq;
   std::memset(&rq.one, 0, sizeof(rq.one));
   rq.tab = t;
-  return launch_any<true>(algo, g, rq, status, head, num_cus, cfg, t.total, stream);
+  return launch_any<true>(algo, g, rq, status, head, num_cus, cfg, false, t.total, stream);
 }
 
 }  // namespace fw
