@@ -25,8 +25,9 @@ struct fw_graph {
   uint64_t bytes = 0;
   uint64_t fingerprint = 0;                        // keys the tuned configurations
   mutable std::atomic<uint64_t> launches{0};       // rotates the head counters
-  mutable std::mutex mu;                           // guards the cache below
+  mutable std::mutex mu;                           // guards the two below
   mutable void* graph_cache = nullptr;             // captured launch graphs
+  mutable void* host_stage = nullptr;              // pinned staging of fw_walk_host
 };
 
 namespace fw {
@@ -52,6 +53,8 @@ uint64_t graph_fingerprint(const fw_graph* g, const uint64_t* off, const uint32_
 hipError_t launch_persistent_checked(const fw_graph* g, const LaunchArgs& a, hipStream_t stream,
                                      bool use_graph, bool staged);
 void release_graph_state(fw_graph* g);
+struct HostStage;
+void free_host_stage(HostStage* s);
 TuneCfg default_tune(const fw_graph* g, int algo, bool staged);
 int validate_tune(const fw_graph* g, const TuneCfg& c, bool staged);
 int autotune(fw_graph* g, int algo, const DevParams& dp, const uint32_t* starts, uint64_t n,

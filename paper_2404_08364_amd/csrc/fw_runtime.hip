@@ -260,6 +260,7 @@ int fw_graph_free(fw_graph* g) {
   (void)hipFree(g->d_status);
   (void)hipFree(g->d_head);
   fw::release_graph_state(g);
+  fw::free_host_stage(static_cast<fw::HostStage*>(g->host_stage));
   delete g;
   return FW_OK;
 }
