@@ -21,7 +21,8 @@ struct TuneCfg {
   uint32_t sum32;       // set per launch: every group total fits in 32 bits
   uint32_t sparse_ratio;  // persistent node2vec: a hop with d(cur) >= ratio *
                           // d(prev) looks N(prev)'s keys up in N(cur) (0: never)
-  uint32_t hub_buckets;   // set per launch: buckets of the workgroup's hub cache
+  uint32_t hub_buckets;      // set per launch: buckets of the workgroup's hub cache,
+  uint32_t hub_few_buckets;  // of 64 and of 16 totals to a row
 };
 
 // max_w * max_f < 2^24: the product of a weight and a factor fits 32 bits

@@ -319,14 +319,13 @@ __device__ __forceinline__ uint32_t row_lower_bound(const uint32_t* __restrict__
 // T_g is below 2^64.  Lane g returns T_g.  Uses the wavefront's LDS region.
 template <class E>
 __device__ __forceinline__ uint64_t sparse_prev_group_totals(const E& ev, const QuadSlice& s,
-                                                             const GroupSplit& sp,
-                                                             const Table& tb, int lane,
-                                                             const Hubs& hubs) {
+                                                             GroupSplit& sp, const Table& tb,
+                                                             int lane, const Hubs& hubs) {
   // Raw totals (weighted rows: streamed, or kept from an earlier visit).
   const char* __restrict__ wrun = reinterpret_cast<const char*>(ev.w + s.a);
   auto quad_raw = [wrun](uint32_t q) { return *reinterpret_cast<const uint4*>(wrun + q * 16u); };
   uint64_t raw = 0;
-  if (ev.w != nullptr && hubs.find(s.d, raw)) {
+  if (ev.w != nullptr && hubs.find(s.d, sp, raw)) {
   } else if (ev.w != nullptr) {
     raw = ev.sum32 ? raw_group_totals<uint32_t>(quad_raw, s, 0, s.nq, sp)
                    : raw_group_totals<uint64_t>(quad_raw, s, 0, s.nq, sp);
@@ -396,10 +395,11 @@ k_walk_persistent(
   Hubs hubs;
   hubs.base = (hub_ptr)(fw_dyn_lds + (blockDim.x / kWave) * cfg.hash_cells);
   hubs.buckets = cfg.hub_buckets;
+  hubs.few_buckets = cfg.hub_few_buckets;
   hubs.cur = kEnd;
   hubs.want = 0;
-  if (hubs.buckets != 0) {
-    clear_hubs(hubs.base, hubs.buckets);
+  if (hubs.few_buckets != 0) {
+    clear_hubs(hubs);
     __syncthreads();  // the only barrier: no wavefront waits for another below
   }
 
@@ -577,7 +577,7 @@ k_walk_persistent(
         // of the merge is merged again from its cursor; otherwise against a
         // hash set of N(prev) (kind 3, when it fits) or by binary searches.
         const QuadSlice qs(o, d);
-        const GroupSplit sp(qs.nq);
+        GroupSplit sp(qs.nq);
         const bool sparse = tb.kind == 3;
         uint64_t gcur = 0;
         const uint64_t mine = sparse ? sparse_prev_group_totals(ev, qs, sp, tb, lane, hubs)
@@ -647,7 +647,9 @@ template <int ALGO, bool W, bool MULTI>
 static hipError_t go(const DevGraph& g, const Reqs<MULTI>& rq, uint32_t* status, uint64_t* head,
                      const TuneCfg& cfg, unsigned blocks, unsigned block, hipStream_t stream) {
   const size_t lds = (size_t)cfg.hash_cells * sizeof(uint32_t) * (block / kWave) +
-                     (size_t)cfg.hub_buckets * kHubBucketWords * sizeof(uint32_t);
+                     ((size_t)cfg.hub_buckets * kHubBucketWords +
+                      (size_t)cfg.hub_few_buckets * kHubFewBucketWords) *
+                         sizeof(uint32_t);
   hipLaunchKernelGGL((k_walk_persistent<ALGO, W, MULTI>), dim3(blocks), dim3(block), lds, stream,
                      g, rq, status, head, cfg);
   return hipGetLastError();
@@ -696,8 +698,8 @@ static hipError_t launch_any(int algo, const DevGraph& g, const Reqs<MULTI>& rq,
     if ((size_t)c.hash_cells * sizeof(uint32_t) * (b / kWave) <= budget) break;
   }
   const size_t regions = (size_t)c.hash_cells * sizeof(uint32_t) * (block / kWave);
-  constexpr size_t kBucketBytes = kHubBucketWords * sizeof(uint32_t);
-  c.hub_buckets = regions < budget ? (uint32_t)((budget - regions) / kBucketBytes) : 0;
+  hub_buckets_in(regions < budget ? (budget - regions) / sizeof(uint32_t) : 0, &c.hub_buckets,
+                 &c.hub_few_buckets);
   const uint64_t per_block = block / kWave;
   const unsigned b = (unsigned)std::max<uint64_t>(1, (waves + per_block - 1) / per_block);
   if ((uint64_t)b * per_block * c.slots < n) {  // only then is the counter claimed from

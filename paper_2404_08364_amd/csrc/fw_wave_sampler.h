@@ -67,17 +67,6 @@ __device__ __forceinline__ void quad_weights(const E& ev, const QuadSlice& s, ui
   }
 }
 
-// Group layout of `len` quads: at most 64 groups of per_group 64-quad chunks.
-struct GroupSplit {
-  uint32_t gsz, groups;
-  __device__ __forceinline__ explicit GroupSplit(uint32_t len) {
-    const uint32_t chunks = (len + kWave - 1) / kWave;
-    const uint32_t per_group = (chunks + kWave - 1) / kWave;
-    gsz = (per_group ? per_group : 1) * kWave;
-    groups = (len + gsz - 1) / gsz;
-  }
-};
-
 // Bit 7 of byte j is set for the entries j of quad q inside the slice.
 __device__ __forceinline__ uint32_t inside_bytes(const QuadSlice& s, uint32_t q) {
   uint32_t m = 0x80808080u;
@@ -315,9 +304,9 @@ __device__ __forceinline__ int64_t wave_descend(const E& ev, const QuadSlice& s,
                                                 uint64_t u, const H& hubs) {
   const int lane = lane_id();
   while (len > (uint32_t)kWave) {
-    const GroupSplit sp(len);
+    GroupSplit sp(len);
     uint64_t mine;
-    if (have_r || !hubs.find(s.d, mine)) {
+    if (have_r || !hubs.find(s.d, sp, mine)) {
       mine = wave_group_totals(ev, s, lo, len, sp);
       if (!have_r) hubs.keep(s.d, mine);
     }

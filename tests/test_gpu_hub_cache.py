@@ -43,14 +43,15 @@ def env():
     small = _hubs(500, 12_000, 1500, 5200, 1000, 3)  # 200+ row keys per workgroup and label
     wide = _hubs(40, 9_000, 2000, 8800, 2**32 - 1, 4)  # group totals past 32 bits among them
     bare = SimpleNamespace(**{**vars(small), "weights": None})
-    return torch, fw, {"small": small, "wide": wide, "bare": bare}
+    long = _hubs(7, 60_000, 32_000, 45_000, 1000, 5)  # around the first region's smallest row
+    return torch, fw, {"small": small, "wide": wide, "bare": bare, "long": long}
 
 
 ALGOS = [("deepwalk", (1, 1, 1), (), (0, 1)), ("ppr", (1, 1, 1), (), (1, 20)),
          ("metapath", (1, 1, 1), (0, 1, 2), (0, 1)), ("node2vec", (2, 3, 5), (), (0, 1))]
 
 
-@pytest.mark.parametrize("graph", ["small", "wide", "bare"])
+@pytest.mark.parametrize("graph", ["small", "wide", "bare", "long"])
 @pytest.mark.parametrize("algo,factors,schema,stop", ALGOS)
 @pytest.mark.parametrize("n,wgs", [(17_000, 4), (700, 0)])
 def test_rows(env, graph, algo, factors, schema, stop, n, wgs):
