@@ -194,7 +194,7 @@ typedef struct fw_tune {
  * (quad q = entries 4q .. 4q + 3), lane 0's entries first.  Both pick
  * neighbour i with chance w'_i / T (Propositions 1 and 2), but not the same
  * neighbour as ITS or as each other.  They run in FW_MODE_PLAIN only; node2vec
- * membership is a binary search of N(prev) per entry, as in the paper. */
+ * membership is an LDS hash set of N(prev), or a binary search of its row. */
 typedef enum { FW_SAMPLER_ITS = 0, FW_SAMPLER_DPRS = 1, FW_SAMPLER_ZPRS = 2 } fw_sampler;
 
 typedef struct fw_walk_opts {

@@ -117,6 +117,53 @@ __device__ __forceinline__ void wave_sync_lds() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// A node2vec hop whose N(prev) is more than this many times longer than
+// N(cur) looks each of N(cur)'s keys up by binary search of N(prev) in global
+// memory (few keys; the top levels of a hub's row stay in cache); a shorter
+// N(prev) goes to the hash set or the merge.  Full passes on one MI355X for
+// ratios 16, 32, 64 and 128: R-MAT-22 node2vec 1308, 1272, 1275 and
+// 1330 ms; Chung-Lu 227M node2vec, 1M queries, 7157, 7084, 7021 and 6992 ms.
+// With the hubs' totals kept, ratios 16, 32 and 64: 524,288 walks on R-MAT-22
+// 133.8, 128.0 and 128.6 ms, 200,003 unweighted walks of 40 hops on Chung-Lu
+// 2^20, whose rows stay in the last-level cache, 17.7, 17.7 and 18.4 ms.
+constexpr uint64_t kSearchRatio = 32;
+
+struct Table {
+  uint32_t base, cells;   // this wavefront's LDS region
+  uint32_t bmask, shift;  // geometry of the hash set
+  int kind;               // 0: global search, 1: hash set, 2: merge of sorted rows
+  uint64_t po, pd;        // N(prev)
+};
+
+// Chooses (and for the hash set builds) the membership structure of N(prev)
+// for one node2vec hop from a vertex of degree d, with the wavefront's lanes.
+__device__ __forceinline__ void build_table(Table& tb, const uint32_t* __restrict__ adj,
+                                            uint64_t d, int lane, bool allow_merge = true) {
+  tb.kind = 0;
+  if (tb.pd == 0 || tb.pd > kSearchRatio * d) return;
+  if (2 * tb.pd > tb.cells) {
+    // Too large for the hash set: merge the sorted rows (the region must
+    // hold at least one 256-entry staging round).
+    if (allow_merge && tb.cells >= 4 * kWave) tb.kind = 2;
+    return;
+  }
+  // The table takes the whole region: a smaller N(prev) gets a lower load,
+  // and a lookup then almost never needs a second bucket (with 64 lanes and
+  // four lookups each, any lane needing one costs the whole wavefront).
+  const uint32_t bits = log2_ceil(tb.cells / 4);  // cells: a power of two >= 64
+  tb.bmask = (1u << bits) - 1;
+  tb.shift = 32 - bits;
+  const uint4 empty = make_uint4(kEnd, kEnd, kEnd, kEnd);
+  for (uint32_t i = lane; i < tb.cells / 4; i += kWave)
+    reinterpret_cast<uint4*>(fw_dyn_lds + tb.base)[i] = empty;
+  wave_sync_lds();
+  for (uint64_t i = lane; i < tb.pd; i += kWave) {
+    hash_insert(tb.base, tb.bmask, tb.shift, adj[tb.po + i]);
+  }
+  wave_sync_lds();
+  tb.kind = 1;
+}
+
 template <int ALGO, bool WEIGHTED, class MEM>
 __device__ __forceinline__ Eval<ALGO, WEIGHTED, MEM> base_eval(const DevGraph& g,
                                                               const DevParams& prm, uint64_t o,

@@ -63,15 +63,16 @@ __device__ __forceinline__ int64_t dprs_pick(const E& ev, uint64_t d, uint64_t s
   return pick;
 }
 
-// The same pick as dprs_pick for rows whose weights are cheap to read twice:
-// the pick is the last selection, so after a first pass for the total T the
-// chunks are visited from the last one, each with the running total that
-// stands before it, and the visit ends at the first chunk that selects.  On
-// average half of the row's Philox blocks are never drawn; they are most of
-// what a chunk costs.  50,021 DeepWalk walks of 20 hops on R-MAT-20: 4.49 ms
-// visiting forwards with queries assigned statically, 1.94 ms so with queries
-// claimed from a counter and the leaner Philox block.  B provides load(q) and weights(v, q, w): the weights
-// of relative quad q (0 past the row), read in two steps, and total(quads).
+// The same pick as dprs_pick for a row in memory: the pick is the last
+// selection, so after a first pass for the total T the chunks are visited from
+// the last one, each with the running total that stands before it, and the
+// visit ends at the first chunk that selects.  On average half of the row's
+// Philox blocks are never drawn; they are most of what a chunk costs.  50,021
+// DeepWalk walks of 20 hops on R-MAT-20: 4.49 ms visiting forwards with queries
+// assigned statically, 1.94 ms so with queries handed out dynamically and the
+// leaner Philox block.  B provides load(q) and weights(v, q, w): the weights
+// (B::Weight) of relative quad q (0 past the row), read in two steps, and
+// total(quads).
 template <class B>
 __device__ __forceinline__ int64_t dprs_pick_back(const B& row, uint32_t d, uint64_t seed,
                                                   uint64_t qid, uint32_t t) {
@@ -86,12 +87,12 @@ __device__ __forceinline__ int64_t dprs_pick_back(const B& row, uint32_t d, uint
     const typename B::Loaded cur = v;
     if (c != 0) v = row.load(c - kWave + lane);  // the next chunk is on its way
     const uint32_t q = c + lane;
-    uint32_t w[4];
+    typename B::Weight w[4];
     row.weights(cur, q, w);
     int64_t sel = -1;
     uint64_t chunk;
     if (small) {
-      const uint32_t s = (w[0] + w[1]) + (w[2] + w[3]);
+      const uint32_t s = (uint32_t)((w[0] + w[1]) + (w[2] + w[3]));
       const uint32_t incl = wave_incl_scan32(s);
       chunk = readlane32(incl, kWave - 1);
       if (chunk != 0) {
@@ -100,10 +101,10 @@ __device__ __forceinline__ int64_t dprs_pick_back(const B& row, uint32_t d, uint
         uint32_t running = (uint32_t)(end - chunk) + incl - s;
 #pragma unroll
         for (uint32_t j = 0; j < 4; ++j) {
-          running += w[j];
+          running += (uint32_t)w[j];
           // floor(u * running / 2^64) for a 32-bit running total.
           const uint64_t m = (u[j] >> 32) * running + (((uint64_t)(uint32_t)u[j] * running) >> 32);
-          if (w[j] != 0 && (uint32_t)(m >> 32) < w[j]) sel = (int64_t)(4 * q + j);
+          if (w[j] != 0 && (uint32_t)(m >> 32) < (uint32_t)w[j]) sel = (int64_t)(4 * q + j);
         }
       }
     } else {
@@ -148,5 +149,30 @@ __device__ __forceinline__ int64_t zprs_pick(const E& ev, uint64_t d, uint64_t s
   return last_selection(sel);
 }
 
+
+// zprs_pick for a row in memory (B as above).
+template <class B>
+__device__ __forceinline__ int64_t zprs_pick_row(const B& row, uint32_t d, uint64_t seed,
+                                                 uint64_t qid, uint32_t t) {
+  const uint32_t quads = (d + 3) / 4;
+  uint64_t mine = 0;
+  for (uint32_t q = (uint32_t)lane_id(); q < quads; q += kWave) {
+    typename B::Weight w[4];
+    row.weights(row.load(q), q, w);
+    mine += ((uint64_t)w[0] + w[1]) + ((uint64_t)w[2] + w[3]);
+  }
+  uint64_t running = wave_incl_scan(mine) - mine;
+  int64_t sel = -1;
+  for (uint32_t q = (uint32_t)lane_id(); q < quads; q += kWave) {
+    typename B::Weight x[4];
+    row.weights(row.load(q), q, x);
+    const uint64_t w[4] = {x[0], x[1], x[2], x[3]};
+    uint64_t u[4];
+    philox4x64_10(qid, t, q, 1, seed, u);
+    const int64_t s = quad_select(w, u, q, running);
+    if (s >= 0) sel = s;
+  }
+  return last_selection(sel);
+}
 
 }  // namespace fw
