@@ -373,6 +373,7 @@ k_walk_persistent(
   uint64_t pool_end = min(pool + cfg.slots, n);
   pool = min(pool, n);
   bool exhausted = pool == n;
+  Claims claims;
   // Draws of 16 hops at a time: lane j of a group holds the one of hop
   // s_t - s_t mod 16 + j, and its bit of `stops` PPR's coin for that hop.  A
   // Philox block is 80 32-bit multiply-adds below the full VALU rate, too many
@@ -389,21 +390,9 @@ k_walk_persistent(
       const uint64_t empty_m = ballot(!s_live && gl == 0 && (uint32_t)grp < cfg.slots);
       const uint32_t empty = __builtin_popcountll(empty_m);
       if (empty) {
-        if (pool == pool_end) {
-          // Claim an eighth of this wavefront's share of what is left (at
-          // least one query per empty group): many short walks then cost few
-          // atomics on the one counter, and the last claims are small.
-          const uint64_t left = n - pool_end;
-          uint64_t k = left / ((uint64_t)waves * 8);
-          k = k < empty ? empty : k > kMaxClaim ? kMaxClaim : k;
-          uint64_t base = 0;
-          if (lane == 0) base = atomicAdd((unsigned long long*)head, (unsigned long long)k);
-          pool = waves * (uint64_t)cfg.slots + readlane64(base, 0);
-          pool_end = pool + k;
-          if (pool >= n) exhausted = true;
-          pool_end = pool_end < n ? pool_end : n;
-          pool = pool < n ? pool : n;
-        }
+        if (pool == pool_end &&
+            !claims.next(head, waves * (uint64_t)cfg.slots, n, waves, empty, pool, pool_end))
+          exhausted = true;
         const uint64_t base = pool;
         const uint64_t next = pool + empty;
         if (!s_live && (uint32_t)grp < cfg.slots) {

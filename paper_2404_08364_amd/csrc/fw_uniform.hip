@@ -63,27 +63,24 @@ k_walk_uniform(DevGraph g, Reqs<MULTI> rq, uint32_t* __restrict__ status,
   bool live = false;
   // The first query of every lane is its own index; the head counter hands
   // out the ones past the grid.
-  bool first = true, exhausted = false;
+  uint64_t pool = uniform64((uint64_t)blockIdx.x * kBlock + (threadIdx.x & ~(uint32_t)(kWave - 1)));
+  uint64_t pool_end = min(pool + kWave, n);
+  pool = min(pool, n);
+  bool exhausted = pool == n;
+  Claims claims;
 
   for (;;) {
     if (!exhausted) {
       const uint64_t empty_m = ballot(!live);
       const uint32_t empty = (uint32_t)__builtin_popcountll(empty_m);
       if (empty >= kClaimMin) {
-        uint64_t base;
-        if (first) {
-          base = (uint64_t)blockIdx.x * kBlock + (threadIdx.x & ~(uint32_t)(kWave - 1));
-          first = false;
-          exhausted = n <= lanes;
-        } else {
-          base = 0;
-          if (lane == 0) base = atomicAdd((unsigned long long*)head, (unsigned long long)empty);
-          base = lanes + readlane64(base, 0);
-          exhausted = base + empty >= n;
-        }
+        if (pool == pool_end &&
+            !claims.next(head, lanes, n, lanes / kWave, empty, pool, pool_end))
+          exhausted = true;
+        const uint64_t base = pool;
         if (!live) {
           const uint64_t q = base + (uint32_t)__builtin_popcountll(empty_m & ((1ull << lane) - 1));
-          if (q < n) {
+          if (q < pool_end) {
             req = rq.find(q);
             const ReqDesc R = rq.get(req);
             const uint64_t lq = q - rq.first(req);
@@ -106,6 +103,8 @@ k_walk_uniform(DevGraph g, Reqs<MULTI> rq, uint32_t* __restrict__ status,
             }
           }
         }
+        pool = pool + empty < pool_end ? pool + empty : pool_end;
+        if (pool == pool_end && (pool_end == n || n <= lanes)) exhausted = true;
       }
     }
     if (!ballot(live)) {

@@ -1,7 +1,6 @@
 """DPRS picked from the last chunk backwards, against the oracle bit for bit:
 rows around one and several 256-entry chunks, totals around 32 bits, rows whose
-last chunks weigh nothing, more queries than wavefronts (claimed from the
-counter)."""
+last chunks weigh nothing, more queries than wavefronts."""
 import numpy as np
 import pytest
 
