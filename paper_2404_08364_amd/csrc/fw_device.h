@@ -31,6 +31,12 @@ struct DevParams {
   uint32_t stop_num, stop_den;  // PPR: stop chance per hop
 };
 
+// A start vertex >= V.  The status word lives in pinned host memory, so that a
+// blocking walk waits for its stream and reads it, without a copy of its own.
+__device__ __forceinline__ void flag_bad_start(uint32_t* status) {
+  __hip_atomic_store(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // ---------------------------------------------------------------------------
 // Philox4x64-10 (Salmon et al., SC 2011): the four words of the block at
 // counter (c0, c1, c2, c3), key (seed, 0).  The step draw is word 0 of the

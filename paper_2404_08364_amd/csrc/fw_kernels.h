@@ -55,7 +55,7 @@ struct LaunchArgs {
   uint64_t seed;
   uint64_t qid_base;
   uint32_t* out;
-  uint32_t* status;     // device: bit 0 set when a start vertex is >= V
+  uint32_t* status;     // set to 1 when a start vertex is >= V
   uint64_t* head;       // device: global task-pool head (persistent form)
   int num_cus;
   uint64_t max_deg;

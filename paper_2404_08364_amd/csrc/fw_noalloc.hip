@@ -64,7 +64,7 @@ extern "C" int fw_walk_noalloc(const fw_graph* g, fw_algo algo, const fw_params*
   a.seed = seed;
   a.qid_base = 0;
   a.out = out_paths;
-  a.status = g->d_status;
+  a.status = g->status;
   a.head = head;
   a.num_cus = g->num_cus;
   a.max_deg = g->max_deg;

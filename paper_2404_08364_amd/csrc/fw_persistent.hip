@@ -405,7 +405,7 @@ k_walk_persistent(
             const uint64_t lq = q - rq.first(r);
             const uint32_t st = R.starts[lq];
             if (st >= g.nv) {
-              if (gl == 0) atomicOr(status, 1u);
+              if (gl == 0) flag_bad_start(status);
             } else {
               if (gl == 0) R.out[lq * ((uint64_t)R.length + 1)] = st;
               if (R.length > 0) {

@@ -286,7 +286,7 @@ int autotune(fw_graph* g, int algo, const DevParams& dp, const uint32_t* starts,
   a.length = length;
   a.seed = seed;
   a.out = out;
-  a.status = g->d_status;
+  a.status = g->status;
   a.head = g->d_head + kHeadStride * (g->launches.fetch_add(1) % kHeadSlots);
   a.num_cus = g->num_cus;
   a.max_deg = g->max_deg;
@@ -372,12 +372,8 @@ int autotune(fw_graph* g, int algo, const DevParams& dp, const uint32_t* starts,
   if (e1) (void)hipEventDestroy(e1);
   (void)hipStreamSynchronize(stream);
   (void)hipFree(out);
-  uint32_t st = 0;
-  (void)hipMemcpy(&st, g->d_status, sizeof(st), hipMemcpyDeviceToHost);
-  if (st) {
-    (void)hipMemset(g->d_status, 0, sizeof(st));
-    if (!rc) rc = set_error(FW_EINVAL, "a start vertex is >= n_vertices");
-  }
+  if (__atomic_exchange_n(g->status, 0u, __ATOMIC_RELAXED) && !rc)
+    rc = set_error(FW_EINVAL, "a start vertex is >= n_vertices");
   if (rc) return rc;
   Tuned t;
   t.persistent = best_p;

@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256) void k_walk_plain(DevGraph g, DevParams prm,
   for (uint64_t q = wave; q < n; q += nwaves) {
     const uint32_t s = uniform32(starts[q]);
     if (s >= g.nv) {
-      if (lane_id() == 0) atomicOr(status, 1u);
+      if (lane_id() == 0) flag_bad_start(status);
       continue;
     }
     RowWriter rw{out + q * ((uint64_t)length + 1), 0, 0, 0};

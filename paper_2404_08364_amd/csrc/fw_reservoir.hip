@@ -133,7 +133,7 @@ __global__ __launch_bounds__(kWave) void k_walk_reservoir(DevGraph g, DevParams 
     const uint32_t s = uniform32(starts[q]);
     uint32_t* row = out + q * ((uint64_t)length + 1);
     if (s >= g.nv) {
-      if (lane == 0) atomicOr(status, 1u);
+      if (lane == 0) flag_bad_start(status);
       continue;
     }
     if (lane == 0) row[0] = s;

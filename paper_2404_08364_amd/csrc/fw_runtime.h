@@ -17,7 +17,7 @@ struct fw_graph {
   uint32_t* d_adj = nullptr;
   uint32_t* d_w = nullptr;
   uint8_t* d_lab = nullptr;
-  uint32_t* d_status = nullptr;  // sticky error bits written by kernels
+  uint32_t* status = nullptr;    // pinned: sticky error word written by kernels
   uint64_t* d_head = nullptr;    // kHeadSlots task-pool heads, one per in-flight launch
   int device = 0;
   int num_cus = 0;

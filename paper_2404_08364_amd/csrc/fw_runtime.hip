@@ -113,16 +113,10 @@ DevGraph dev_graph(const fw_graph* g) {
 }
 
 int read_status(const fw_graph* g, hipStream_t stream) {
-  uint32_t st = 0;
-  hipError_t e = hipMemcpyAsync(&st, g->d_status, sizeof(st), hipMemcpyDeviceToHost, stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(stream);
-  if (e != hipSuccess) return hip_fail(e, "reading the walk status");
-  if (st) {
-    e = hipMemsetAsync(g->d_status, 0, sizeof(uint32_t), stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) return hip_fail(e, "clearing the walk status");
+  const hipError_t e = hipStreamSynchronize(stream);
+  if (e != hipSuccess) return hip_fail(e, "waiting for the walk");
+  if (__atomic_exchange_n(g->status, 0u, __ATOMIC_RELAXED))
     return fail(FW_EINVAL, "a start vertex is >= n_vertices");
-  }
   return FW_OK;
 }
 
@@ -229,7 +223,8 @@ int fw_graph_upload(const fw_csr* csr, const uint32_t* weights, const uint8_t* l
   if (e == hipSuccess) e = hipMemset(g->d_adj + ne, 0, kPad * sizeof(uint32_t));
   if (e == hipSuccess && weights) e = hipMemset(g->d_w + ne, 0, kPad * sizeof(uint32_t));
   if (e == hipSuccess && labels) e = hipMemset(g->d_lab + ne, 0, kPad);
-  if (e == hipSuccess) e = alloc((void**)&g->d_status, 256);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&g->status, 256, 0);
+  if (e == hipSuccess) *g->status = 0;
   if (e == hipSuccess)
     e = alloc((void**)&g->d_head, fw::kHeadSlots * fw::kHeadStride * sizeof(uint64_t));
   if (e == hipSuccess) e = hipMemcpy(g->d_off, off, (nv + 1) * sizeof(uint64_t), hipMemcpyHostToDevice);
@@ -237,7 +232,6 @@ int fw_graph_upload(const fw_csr* csr, const uint32_t* weights, const uint8_t* l
   if (e == hipSuccess && weights && ne)
     e = hipMemcpy(g->d_w, weights, ne * sizeof(uint32_t), hipMemcpyHostToDevice);
   if (e == hipSuccess && labels && ne) e = hipMemcpy(g->d_lab, labels, ne, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemset(g->d_status, 0, 256);
   if (e == hipSuccess)
     e = hipMemset(g->d_head, 0, fw::kHeadSlots * fw::kHeadStride * sizeof(uint64_t));
   if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -257,7 +251,7 @@ int fw_graph_free(fw_graph* g) {
   (void)hipFree(g->d_adj);
   (void)hipFree(g->d_w);
   (void)hipFree(g->d_lab);
-  (void)hipFree(g->d_status);
+  if (g->status) (void)hipHostFree(g->status);
   (void)hipFree(g->d_head);
   fw::release_graph_state(g);
   fw::free_host_stage(static_cast<fw::HostStage*>(g->host_stage));
@@ -298,7 +292,7 @@ int fw_walk_ex(const fw_graph* g, fw_algo algo, const fw_params* params,
   a.seed = seed;
   a.qid_base = o.qid_base;
   a.out = out_paths;
-  a.status = g->d_status;
+  a.status = g->status;
   a.head = g->d_head + fw::kHeadStride * (g->launches.fetch_add(1) % fw::kHeadSlots);
   a.num_cus = g->num_cus;
   a.max_deg = g->max_deg;

@@ -307,7 +307,7 @@ __global__ __launch_bounds__(NW* kWave) void k_walk_persistent(
             if (q < n) {
               const uint32_t st = starts[q];
               if (st >= g.nv) {
-                atomicOr(status, 1u);
+                flag_bad_start(status);
               } else {
                 out[q * ((uint64_t)length + 1)] = st;
                 if (length > 0) {

@@ -106,7 +106,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_walk_team(
   const uint64_t query = blockIdx.x;
   uint32_t cur = uniform32(starts[query]);
   if (cur >= g.nv) {
-    if (threadIdx.x == 0) atomicOr(status, 1u);
+    if (threadIdx.x == 0) flag_bad_start(status);
     return;
   }
   uint32_t* __restrict__ row = out + query * ((uint64_t)length + 1);

@@ -86,7 +86,7 @@ k_walk_uniform(DevGraph g, Reqs<MULTI> rq, uint32_t* __restrict__ status,
             const uint64_t lq = q - rq.first(req);
             cur = R.starts[lq];
             if (cur >= g.nv) {
-              atomicOr(status, 1u);
+              flag_bad_start(status);
             } else {
               length = R.length;
               row = R.out + lq * ((uint64_t)length + 1);
