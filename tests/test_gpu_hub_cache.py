@@ -64,3 +64,25 @@ def test_rows(env, graph, algo, factors, schema, stop, n, wgs):
     exp = oracle.walk(g, algo, oracle.params(*factors, schema=schema, stop=stop), starts, 6, 21)
     assert_rows_equal(got, exp, f"{algo} on {graph} n={n}")
     G.free()
+
+
+@pytest.mark.parametrize("over", [0, 1])
+@pytest.mark.parametrize("algo,factors", [("deepwalk", (1, 1, 1)), ("node2vec", (2, 3, 5))])
+def test_totals_around_32_bits(env, algo, factors, over):
+    """Every weight at the largest value whose group totals are summed in 32
+    bits (2^32 over the factor and d / 64 + 512 entries), and one above it."""
+    torch, fw, _ = env
+    d = 70_001
+    limit = (2**32 - 1) // (max(factors) * (d // 64 + 512)) + over
+    off = np.concatenate([[0, d], d + 1 + np.arange(d)]).astype(np.uint64)
+    adj = np.concatenate([1 + np.arange(d), np.zeros(d)]).astype(np.uint32)
+    g = SimpleNamespace(offsets=off, adj=adj, weights=np.full(2 * d, limit, np.uint32),
+                        labels=None, n_vertices=d + 1, n_edges=2 * d)
+    G = fw.Graph.of(g)
+    starts = np.concatenate([np.zeros(40), np.arange(1, 60)]).astype(np.uint32)
+    exp = oracle.walk(g, algo, oracle.params(*factors), starts, 5, 31)
+    for tune in (None, fw.make_tune(wgs_per_cu=8)):
+        got = gpu_walk(torch, fw, G, algo, fw.make_params(factors), starts, 5, 31, "persistent",
+                       tune=tune)
+        assert_rows_equal(got, exp, f"{algo} over={over}")
+    G.free()
