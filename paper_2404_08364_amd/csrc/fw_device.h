@@ -377,38 +377,47 @@ struct Eval {
   // The quad's transition weights, entries outside the slice included: the
   // caller masks them.
   __device__ __forceinline__ void weights(const Loaded& v, uint64_t out[4]) const {
+    if (ALGO == kNode2Vec && !first) {
+      biased_weights(v.w, v.a, out);
+      return;
+    }
     const uint32_t wq[4] = {v.w.x, v.w.y, v.w.z, v.w.w};
-    if (ALGO == kNode2Vec) {
-      if (first) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) out[j] = wq[j];
-        return;
-      }
-      const uint32_t u[4] = {v.a.x, v.a.y, v.a.z, v.a.w};
-      // f_in for a neighbour of prev, f_out otherwise, then f_ret for prev.
-      uint32_t f[4];
-      mem.factors4(u, f_in, f_out, f);
-      const uint32_t fr = f_ret;
+    for (int j = 0; j < 4; ++j)
+      out[j] = ALGO != kMetaPath || ((v.l >> (8 * j)) & 0xFFu) == want ? wq[j] : 0ull;
+  }
+  // Eq. 2 times the weights.
+  __device__ __forceinline__ void biased_weights(uint4 w4, uint4 a, uint64_t out[4]) const {
+    const uint32_t wq[4] = {w4.x, w4.y, w4.z, w4.w};
+    const uint32_t u[4] = {a.x, a.y, a.z, a.w};
+    // f_in for a neighbour of prev, f_out otherwise, then f_ret for prev.
+    uint32_t f[4];
+    mem.factors4(u, f_in, f_out, f);
+    const uint32_t fr = f_ret;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) f[j] = u[j] == prev ? fr : f[j];
-      if (narrow) {
-        // (HIP's __umul24 returns a signed int: go through uint32_t.)
+    for (int j = 0; j < 4; ++j) f[j] = u[j] == prev ? fr : f[j];
+    if (narrow) {
+      // (HIP's __umul24 returns a signed int: go through uint32_t.)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) out[j] = (uint64_t)(uint32_t)__umul24(wq[j], f[j]);
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) out[j] = (uint64_t)wq[j] * f[j];
-      }
-    } else if (ALGO == kMetaPath) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) out[j] = (((v.l >> (8 * j)) & 0xFFu) == want) ? wq[j] : 0ull;
+      for (int j = 0; j < 4; ++j) out[j] = (uint64_t)(uint32_t)__umul24(wq[j], f[j]);
     } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) out[j] = wq[j];
+      for (int j = 0; j < 4; ++j) out[j] = (uint64_t)wq[j] * f[j];
     }
   }
+  // Both at once, with one branch on `first`.
   __device__ __forceinline__ void quad(uint32_t q, uint64_t out[4]) const {
-    weights(load(q), out);
+    if (ALGO == kNode2Vec && !first) {
+      biased_weights(WEIGHTED ? quad_raw(q) : make_uint4(1u, 1u, 1u, 1u), quad_ids(q), out);
+      return;
+    }
+    Loaded v{make_uint4(1u, 1u, 1u, 1u), make_uint4(0u, 0u, 0u, 0u), 0u};
+    if (WEIGHTED) v.w = quad_raw(q);
+    if (ALGO == kMetaPath) v.l = quad_labels(q);
+    const uint32_t wq[4] = {v.w.x, v.w.y, v.w.z, v.w.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      out[j] = ALGO != kMetaPath || ((v.l >> (8 * j)) & 0xFFu) == want ? wq[j] : 0ull;
   }
 };
 
