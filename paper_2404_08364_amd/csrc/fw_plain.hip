@@ -4,9 +4,15 @@
 // query-centric baseline that section 5.2 argues against on GPUs; the
 // persistent form (fw_persistent.hip) adds dynamic scheduling.
 #include "fw_kernels.h"
+#include "fw_member.h"
 #include "fw_wave_sampler.h"
 
 namespace fw {
+
+// LDS cells of a wavefront's hash set of N(prev) (node2vec; longer rows are
+// searched in global memory).  100,000 walks of 20 hops on R-MAT-20: 10.4 ms
+// with searches alone, 7.75 ms so.
+constexpr uint32_t kCells = 1024;
 
 // Buffers a path row in the lanes of a wavefront (lane k holds entry
 // base + k) and stores 64 entries at a time.
@@ -52,31 +58,28 @@ __global__ __launch_bounds__(256) void k_walk_plain(DevGraph g, DevParams prm,
     RowWriter rw{out + q * ((uint64_t)length + 1), 0, 0, 0};
     rw.push(s);
     uint32_t cur = s, prev = kEnd;
+    uint64_t po = 0, pd = 0;
     uint32_t t = 0;
     for (; t < length; ++t) {
       if (ALGO == kPPR && ppr_stops(prm, seed, qid_base + q, t)) break;
       const uint64_t o = g.off[cur];
       const uint64_t d = g.off[cur + 1] - o;
-      Eval<ALGO, WEIGHTED> ev;
-      ev.adj = g.adj;
-      ev.w = g.w;
-      ev.lab = g.lab;
-      ev.o = o;
-      ev.first = (t == 0);
+      auto ev = base_eval<ALGO, WEIGHTED, MemberAny>(g, prm, o, prev, t);
       if (ALGO == kNode2Vec) {
-        ev.prev = prev;
-        ev.f_ret = prm.f_ret;
-        ev.f_in = prm.f_in;
-        ev.f_out = prm.f_out;
+        Table tb;
+        tb.cells = kCells;
+        tb.base = (threadIdx.x / kWave) * kCells;
+        tb.po = po;
+        tb.pd = t > 0 ? pd : 0;
+        build_table(tb, g.adj, d, lane_id(), false);
+        ev.mem.mode = tb.kind;
+        ev.mem.base = tb.base;
+        ev.mem.bmask = tb.bmask;
+        ev.mem.shift = tb.shift;
         ev.mem.adj = g.adj;
-        if (t > 0) {
-          ev.mem.po = g.off[prev];
-          ev.mem.pd = g.off[prev + 1] - ev.mem.po;
-        } else {
-          ev.mem.po = ev.mem.pd = 0;
-        }
+        ev.mem.po = tb.po;
+        ev.mem.pd = tb.pd;
       }
-      if (ALGO == kMetaPath) ev.want = schema_label(prm, t);
       const uint64_t u = philox_draw(seed, qid_base + q, t);
       int64_t idx;
       if ((ALGO == kDeepWalk || ALGO == kPPR) && !WEIGHTED) {
@@ -90,6 +93,9 @@ __global__ __launch_bounds__(256) void k_walk_plain(DevGraph g, DevParams prm,
       rw.push(nxt);
       prev = cur;
       cur = nxt;
+      po = o;  // the next hop's N(prev)
+      pd = d;
+      if (ALGO == kNode2Vec) wave_sync_lds();
     }
     rw.finish(length);
   }
@@ -104,7 +110,8 @@ hipError_t launch_plain(const LaunchArgs& a, hipStream_t stream) {
   if (blocks == 0) blocks = 1;
   const bool wt = a.g.w != nullptr;
 #define FW_GO(A, W)                                                                         \
-  hipLaunchKernelGGL((k_walk_plain<A, W>), dim3((unsigned)blocks), dim3(block), 0, stream,  \
+  hipLaunchKernelGGL((k_walk_plain<A, W>), dim3((unsigned)blocks), dim3(block),             \
+                     A == kNode2Vec ? block / kWave * kCells * sizeof(uint32_t) : 0, stream, \
                      a.g, a.prm, a.starts, a.n, a.length, a.seed, a.qid_base, a.out,         \
                      a.status)
   switch (a.algo) {

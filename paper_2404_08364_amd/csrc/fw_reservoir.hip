@@ -30,7 +30,7 @@
 namespace fw {
 
 // LDS cells of a wavefront's hash set of N(prev).
-constexpr uint32_t kCells = 1024;
+constexpr uint32_t kSetCells = 1024;
 
 template <int ALGO>
 struct WeightOf {
@@ -159,8 +159,8 @@ __global__ __launch_bounds__(kWave) void k_walk_reservoir(DevGraph g, DevParams 
           rq.f_in = prm.f_in;
           rq.f_out = prm.f_out;
           Table tb;
-          tb.cells = kCells;
-          tb.base = (threadIdx.x / kWave) * kCells;
+          tb.cells = kSetCells;
+          tb.base = (threadIdx.x / kWave) * kSetCells;
           tb.po = po;
           tb.pd = t == 0 ? 0 : pd;
           build_table(tb, g.adj, d, lane, false);
@@ -201,7 +201,7 @@ hipError_t launch_reservoir(const LaunchArgs& a, int sampler, hipStream_t stream
   const bool zz = sampler == 2;
 #define FW_GO(A, W, Z)                                                                          \
   hipLaunchKernelGGL((k_walk_reservoir<A, W, Z>), dim3((unsigned)blocks), dim3(block),          \
-                     A == kNode2Vec ? block / kWave * kCells * sizeof(uint32_t) : 0, stream,    \
+                     A == kNode2Vec ? block / kWave * kSetCells * sizeof(uint32_t) : 0, stream,    \
                      a.g, a.prm, a.starts, a.n, a.length, a.seed, a.qid_base, a.out, a.status)
 #define FW_GO2(A)                                 \
   if (wt) {                                       \
