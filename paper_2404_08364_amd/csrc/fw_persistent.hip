@@ -16,7 +16,7 @@
 //
 // Node2vec membership in N(prev) for non-tiny hops uses the wavefront's LDS
 // region: an exact 4-cell-bucket hash set of N(prev) when it fits; otherwise,
-// while N(prev) is at most 64x N(cur), a merge of the two sorted rows (each
+// while N(prev) is at most 32x N(cur), a merge of the two sorted rows (each
 // 256-entry chunk of N(cur) stages the window of N(prev) that holds its value
 // range into LDS and searches it there); when N(prev) is much larger than
 // N(cur), binary search of the sorted row in global memory.  The group totals
