@@ -42,6 +42,8 @@ constexpr int kGroupLanes = 16;
 constexpr int kMaxBlock = 1024;  // threads per workgroup
 constexpr size_t kCuLds = 160 * 1024;
 constexpr size_t kLdsGrain = 1280;  // LDS is handed out in these steps
+// 256-thread workgroups a CU holds (eight wavefronts per SIMD, below).
+constexpr uint32_t kCuWgs = 8;
 constexpr uint32_t kMaxRoomyCells = 4096;
 
 using lds_ptr = const __attribute__((address_space(3))) uint32_t*;
@@ -622,11 +624,15 @@ static hipError_t launch_any(int algo, const DevGraph& g, const Reqs<MULTI>& rq,
   }
   // Wavefronts: at most wgs_per_cu times four per CU, each with up to four
   // queries, and one while there are wavefronts for all (a wavefront runs
-  // the long hops of its queries one after the other).  Where they fill the chip they run in workgroups as large as the
-  // configuration divides into, which share one hub cache in what the
-  // regions leave of their part of the LDS; a smaller launch spreads over the
-  // CUs in workgroups of four wavefronts.  3,001 node2vec walks of 80 hops on
-  // R-MAT-20: 6.59 ms with four queries to each of 751 wavefronts, 2.40 ms so.
+  // the long hops of its queries one after the other).  Where they fill the
+  // chip they run in workgroups as large as the configuration divides into,
+  // which share one hub cache in what the regions leave of their part of the
+  // LDS; a smaller launch spreads over the CUs in workgroups of four
+  // wavefronts.  3,001 node2vec walks of 80 hops on R-MAT-20: 6.59 ms with four
+  // queries to each of 751 wavefronts, 2.40 ms so.
+  // A workgroup's part is that of its wavefronts in a full CU, also where the
+  // configuration asks for fewer: then other launches run beside this one (the
+  // server's express lane and its bulk streams) and have to find room.
   const uint64_t full = (uint64_t)num_cus * c.wgs_per_cu * 4;
   c.slots = (uint32_t)std::min<uint64_t>(kGroups, (n + full - 1) / full);
   if (c.slots == 0) c.slots = 1;
@@ -636,7 +642,7 @@ static hipError_t launch_any(int algo, const DevGraph& g, const Reqs<MULTI>& rq,
   for (uint32_t b : {1024u, 512u, 256u}) {
     const uint32_t per = b / 256;
     if (c.wgs_per_cu % per || (b > 256 && waves < full)) continue;
-    budget = kCuLds / (c.wgs_per_cu / per) / kLdsGrain * kLdsGrain;
+    budget = kCuLds * per / std::max(c.wgs_per_cu, kCuWgs) / kLdsGrain * kLdsGrain;
     block = b;
     if ((size_t)c.hash_cells * sizeof(uint32_t) * (b / kWave) <= budget) break;
   }
