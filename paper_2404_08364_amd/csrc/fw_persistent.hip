@@ -44,7 +44,6 @@ constexpr size_t kCuLds = 160 * 1024;
 constexpr size_t kLdsGrain = 1280;  // LDS is handed out in these steps
 // 256-thread workgroups a CU holds (eight wavefronts per SIMD, below).
 constexpr uint32_t kCuWgs = 8;
-constexpr uint32_t kMaxRoomyCells = 4096;
 
 using lds_ptr = const __attribute__((address_space(3))) uint32_t*;
 
@@ -602,8 +601,8 @@ static hipError_t go(const DevGraph& g, const Reqs<MULTI>& rq, uint32_t* status,
 
 template <bool MULTI>
 static hipError_t launch_any(int algo, const DevGraph& g, const Reqs<MULTI>& rq, uint32_t* status,
-                             uint64_t* head, int num_cus, const TuneCfg& tuned, bool roomy,
-                             uint64_t n, hipStream_t stream) {
+                             uint64_t* head, int num_cus, const TuneCfg& tuned, uint64_t n,
+                             hipStream_t stream) {
   TuneCfg c = tuned;
   if (c.tiny_max > 16 || c.wgs_per_cu == 0 || c.hash_cells < 64 ||
       (c.hash_cells & (c.hash_cells - 1)) || head == nullptr)
@@ -613,15 +612,6 @@ static hipError_t launch_any(int algo, const DevGraph& g, const Reqs<MULTI>& rq,
   if (!wt && (algo == kDeepWalk || algo == kPPR))
     return launch_uniform<MULTI>(algo, g, rq, status, head, num_cus, c.wgs_per_cu, n, stream);
   if (algo != kNode2Vec) c.hash_cells = 0;  // only node2vec uses the regions
-  if (roomy && algo == kNode2Vec) {
-    // Fewer wavefronts than the configuration is for: larger regions, so that
-    // more rows go to the hash set instead of the merge (4,096 walks of 40 hops
-    // on R-MAT-20: 1.27 ms with 1,024 cells each, 1.16 ms with 2,048).
-    const uint64_t waves_per_cu = (n + num_cus - 1) / num_cus;
-    while (c.hash_cells < kMaxRoomyCells &&
-           2 * c.hash_cells * sizeof(uint32_t) * (waves_per_cu + 4) <= kCuLds)
-      c.hash_cells *= 2;
-  }
   // Wavefronts: at most wgs_per_cu times four per CU, each with up to four
   // queries, and one while there are wavefronts for all (a wavefront runs
   // the long hops of its queries one after the other).  Where they fill the
@@ -630,9 +620,12 @@ static hipError_t launch_any(int algo, const DevGraph& g, const Reqs<MULTI>& rq,
   // LDS; a smaller launch spreads over the CUs in workgroups of four
   // wavefronts.  3,001 node2vec walks of 80 hops on R-MAT-20: 6.59 ms with four
   // queries to each of 751 wavefronts, 2.40 ms so.
-  // A workgroup's part is that of its wavefronts in a full CU, also where the
-  // configuration asks for fewer: then other launches run beside this one (the
-  // server's express lane and its bulk streams) and have to find room.
+  // A workgroup's part is that of its wavefronts in a full CU, also where there
+  // are fewer: then other launches run beside this one (the server's express
+  // lane and its bulk streams, walks on other streams) and have to find room.
+  // Node2vec regions grown to what the missing wavefronts leave: 4,096 walks of
+  // 40 hops on R-MAT-20 1.10 against 1.22 ms alone, 2.14 against 1.49 ms with
+  // a second such launch beside.
   const uint64_t full = (uint64_t)num_cus * c.wgs_per_cu * 4;
   c.slots = (uint32_t)std::min<uint64_t>(kGroups, (n + full - 1) / full);
   if (c.slots == 0) c.slots = 1;
@@ -686,7 +679,7 @@ hipError_t launch_persistent(const LaunchArgs& a, hipStream_t stream) {
   rq.one.prm = a.prm;
   rq.tab = ReqTable{nullptr, nullptr, 0, 0};
   return launch_any<false>(a.algo, a.g, rq, a.status, a.head, a.num_cus, a.cfg,
-                           !a.tuned_by_caller, a.n, stream);
+                           a.n, stream);
 }
 
 hipError_t launch_persistent_multi(int algo, const DevGraph& g, const ReqTable& t,
@@ -695,7 +688,7 @@ hipError_t launch_persistent_multi(int algo, const DevGraph& g, const ReqTable& 
   Reqs<true> rq;
   std::memset(&rq.one, 0, sizeof(rq.one));
   rq.tab = t;
-  return launch_any<true>(algo, g, rq, status, head, num_cus, cfg, false, t.total, stream);
+  return launch_any<true>(algo, g, rq, status, head, num_cus, cfg, t.total, stream);
 }
 
 }  // namespace fw

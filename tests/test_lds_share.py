@@ -92,3 +92,25 @@ print(json.dumps(out))
     for a, (lds, grid, block) in got.items():
         assert (grid, block) == (2 * CUS, 1024)
         assert CU_LDS * 0.97 < lds <= CU_LDS, a
+
+
+@pytest.mark.parametrize("hub", [0, 9000])
+def test_launches_of_few_wavefronts(host_hip, hub):  # noqa: F811
+    """A launch that leaves wavefront slots free leaves as large a part of the
+    LDS for the launches of other streams."""
+    got = json.loads(host_hip(COMMON + f"""
+g = ring(hub={hub})
+st = np.zeros(8000, np.uint32)
+rows = np.zeros((8000, 5), np.uint32)
+for a in {ALGOS!r}:
+    for n in (769, 1024, 1500, 3073, 3500, 4096, 5000, 8000):
+        launches()
+        assert fw.walk_ptr(g, a, prm[a], st.ctypes.data, n, 4, 1, rows.ctypes.data) == 0
+        (l,) = launches()
+        if b"k_walk_persistent" in l.name:
+            out[f"{{a}} {{n}}"] = (cu_lds(l), -(-l.grid // 256) * l.block // 256)
+print(json.dumps(out))
+"""))
+    assert any(k.startswith("node2vec 4096") for k in got)
+    for k, (lds, wgs) in got.items():
+        assert lds <= CU_LDS * wgs // 8, k
