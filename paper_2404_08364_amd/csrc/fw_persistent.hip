@@ -640,8 +640,10 @@ static hipError_t launch_any(int algo, const DevGraph& g, const Reqs<MULTI>& rq,
     if ((size_t)c.hash_cells * sizeof(uint32_t) * (b / kWave) <= budget) break;
   }
   const size_t regions = (size_t)c.hash_cells * sizeof(uint32_t) * (block / kWave);
-  hub_buckets_in(regions < budget ? (budget - regions) / sizeof(uint32_t) : 0, &c.hub_buckets,
-                 &c.hub_few_buckets);
+  // Of node2vec's passes only the regrouped totals read kept sums, of weights.
+  const bool hubs = algo != kNode2Vec || (wt && c.sparse_ratio != 0);
+  hub_buckets_in(hubs && regions < budget ? (budget - regions) / sizeof(uint32_t) : 0,
+                 &c.hub_buckets, &c.hub_few_buckets);
   const uint64_t per_block = block / kWave;
   const unsigned b = (unsigned)std::max<uint64_t>(1, (waves + per_block - 1) / per_block);
   if ((uint64_t)b * per_block * c.slots < n) {  // only then is the counter claimed from

@@ -114,3 +114,28 @@ print(json.dumps(out))
     assert any(k.startswith("node2vec 4096") for k in got)
     for k, (lds, wgs) in got.items():
         assert lds <= CU_LDS * wgs // 8, k
+
+
+def test_no_hub_totals_where_none_are_read(host_hip):  # noqa: F811
+    """Only node2vec's regrouped totals of weighted rows read the hub totals:
+    without weights, or without that pass, a launch takes its regions alone."""
+    got = json.loads(host_hip(COMMON + """
+st = np.zeros(400000, np.uint32)
+rows = np.zeros((400000, 5), np.uint32)
+for what, kw, tune in (("unweighted", dict(weights=None), dict(hash_cells=1024)),
+                       ("unweighted small", dict(weights=None), dict(hash_cells=256)),
+                       ("never", {}, dict(hash_cells=512, sparse_ratio=0xFFFFFFFF)),
+                       ("weighted", {}, dict(hash_cells=512))):
+    g = ring(hub=9000, **kw)
+    launches()
+    assert fw.walk_ptr(g, "node2vec", prm["node2vec"], st.ctypes.data, st.size, 4, 1,
+                       rows.ctypes.data, tune=fw.make_tune(**tune)) == 0
+    (l,) = launches()
+    out[what] = (l.lds, l.block // 64 * tune["hash_cells"] * 4)
+print(json.dumps(out))
+"""))
+    for what, (lds, regions) in got.items():
+        if what == "weighted":
+            assert lds > regions
+        else:
+            assert lds == regions, what
