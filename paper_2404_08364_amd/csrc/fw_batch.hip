@@ -266,7 +266,11 @@ int fw_walk_host(const fw_graph* g, fw_algo algo, const fw_params* params,
     uint8_t* dst = out_of(s);
     on_threads(k, [&](unsigned i) {
       const uint64_t lo = row_bytes * i / k, hi = row_bytes * (i + 1) / k;
-      for (uint64_t p = lo; p < hi; p += kPage) reinterpret_cast<volatile uint8_t*>(dst)[p] = 0;
+      for (uint64_t p = lo; p < hi; p += kPage) {
+        uint8_t none = 0;  // an access that writes (one fault), and leaves every byte as it is
+        (void)__atomic_compare_exchange_n(dst + p, &none, (uint8_t)0, false, __ATOMIC_RELAXED,
+                                          __ATOMIC_RELAXED);
+      }
     });
     if (b) rc = drain(side[(b + 1) % 2]);
   }

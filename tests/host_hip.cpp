@@ -34,6 +34,7 @@ std::vector<Launch> launches;
 std::atomic<long> fail_at{-1};  // this launch and those after it fail
 std::atomic<uintptr_t> handles{0x1000};
 thread_local std::vector<Config> configs;
+thread_local hipError_t last_error = hipSuccess;
 
 template <class T>
 hipError_t handle(T* out) {
@@ -87,7 +88,8 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void**, size_t lds,
                            hipStream_t stream) {
   std::lock_guard<std::mutex> lk(mu);
-  if (fail_at >= 0 && (long)launches.size() >= fail_at) return hipErrorLaunchFailure;
+  if (fail_at >= 0 && (long)launches.size() >= fail_at)
+    return last_error = hipErrorLaunchFailure;
   Launch l{};
   std::strncpy(l.name, names[f].c_str(), sizeof(l.name) - 1);
   l.grid = grid.x;
@@ -110,7 +112,11 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600* p, int) {
   return hipSuccess;
 }
 hipError_t hipGetSymbolAddress(void** p, const void*) { return memory(p, 4096); }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError() {
+  const hipError_t e = last_error;
+  last_error = hipSuccess;
+  return e;
+}
 const char* hipGetErrorString(hipError_t) { return "host runtime error"; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 
