@@ -323,22 +323,15 @@ struct Eval {
     }
   }
 
-  // Total transition weight of quad q (all four entries, so interior quads
-  // only).  Unweighted MetaPath counts the matching labels of the quad's
-  // word in a few bit operations (kCheapTotal: the streaming pass then takes
-  // several quads per lane at once); everything else sums quad().
+  // Unweighted MetaPath: a quad's total is the count of matching labels in its
+  // word, a few bit operations; the streaming pass then takes several quads
+  // per lane at once (cheap_group_totals).
   static constexpr bool kCheapTotal = ALGO == kMetaPath && !WEIGHTED;
   // Weighted DeepWalk and PPR: a quad's transition weights are its raw
   // weights (one 16-byte load, quad_raw).
   static constexpr bool kRawWeights = (ALGO == kDeepWalk || ALGO == kPPR) && WEIGHTED;
   __device__ __forceinline__ uint4 quad_raw(uint32_t q) const {
     return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(w + qa) + q * 16u);
-  }
-  __device__ __forceinline__ uint64_t quad_total4(uint32_t q) const {
-    if (ALGO == kMetaPath && !WEIGHTED) return (uint64_t)__builtin_popcount(quad_match(q));
-    uint64_t o[4];
-    quad(q, o);
-    return (o[0] + o[1]) + (o[2] + o[3]);
   }
 
   // Unweighted MetaPath: bit 7 of byte j is set iff entry j of quad q

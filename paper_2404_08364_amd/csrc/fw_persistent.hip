@@ -2,17 +2,19 @@
 // for wave64).
 //
 // A fixed grid of wavefronts stays resident.  Each wavefront keeps a local
-// task pool of four live queries, one per 16-lane group (query id, current
-// and previous vertex, hop index, cached CSR range; every lane of a group
-// holds a copy), and refills empty entries from the global task pool with one
-// 64-bit atomicAdd on a head counter.  Every round advances each live query
-// by one hop:
+// task pool of up to four live queries (one where the launch has no more
+// queries than wavefronts), one per 16-lane group (query id, current and
+// previous vertex, hop index, cached CSR range; every lane of a group holds a
+// copy).  Its first queries are its own by index; it refills empty entries
+// from the global task pool, which it claims several queries at a time from
+// with a 64-bit atomicAdd on a head counter (Claims in fw_requests.h).  Every
+// round advances each live query by one hop:
 //   * tiny hops (degree <= tiny_max <= 16) run together, one per 16-lane
 //     group: a row-wide DPP scan, a draw per group, a ballot;
 //   * every other hop runs on the whole wavefront, one query after the
 //     other, with the quad-streaming sampler of fw_wave_sampler.h.
-// There are no workgroup barriers: wavefronts never wait for each other, so
-// every resident wavefront keeps its loads in flight.
+// After one barrier, once the workgroup's kept totals are cleared, no wavefront
+// waits for another, so every resident wavefront keeps its loads in flight.
 //
 // Node2vec membership in N(prev) for non-tiny hops uses the wavefront's LDS
 // region: an exact 4-cell-bucket hash set of N(prev) when it fits; otherwise,

@@ -227,8 +227,9 @@ hipError_t launch_batch(fw_server* s, Batch& b) {
       fw::TuneCfg cfg = s->cfg[a];
       if (s->opts.express_max_queries) {
         // The express lane keeps kExpressWgs workgroups per CU for itself;
-        // the bulk streams share the rest, so an express launch always finds
-        // room instead of waiting for persistent launches to drain.
+        // the bulk streams (up to six) share the rest, each launch with the LDS
+        // of its wavefronts, so an express launch finds room instead of
+        // waiting for persistent launches to drain.
         const uint32_t bulk = s->opts.max_inflight - 1;
         const uint32_t w = b.express ? kExpressWgs
                                      : std::max<uint32_t>(1, (cfg.wgs_per_cu - kExpressWgs) / bulk);

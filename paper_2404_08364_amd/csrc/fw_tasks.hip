@@ -33,11 +33,6 @@ struct TaskEval {
   static constexpr bool kCheapTotal = false;
   static constexpr bool kRawWeights = false;
   static constexpr bool sum32 = false;
-  __device__ __forceinline__ uint64_t quad_total4(uint32_t q) const {
-    uint64_t o[4];
-    quad(q, o);
-    return (o[0] + o[1]) + (o[2] + o[3]);
-  }
   __device__ __forceinline__ void quad(uint32_t q, uint64_t out[4]) const {
     const uint64_t p = qa + 4ull * q;
     if (p + 4 <= end) {
