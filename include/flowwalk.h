@@ -139,9 +139,9 @@ int fw_walk(const fw_graph* g, fw_algo algo, const fw_params* params, const uint
  *                       (no load balancing: the baseline).
  *   FW_MODE_PERSISTENT  persistent wavefronts that claim queries from a
  *                       global atomic head (dynamic scheduling, section 5.2);
- *                       each keeps four queries, batches tiny-degree hops
- *                       four to a wavefront and runs the others on the whole
- *                       wavefront (sampler organisation of section 5.1).
+ *                       each keeps up to four queries, batches tiny-degree
+ *                       hops four to a wavefront and runs the others on the
+ *                       whole wavefront (sampler organisation of section 5.1).
  *                       Launches of few queries that pass no fw_tune take a
  *                       workgroup per query instead; unweighted DeepWalk and
  *                       PPR a lane per query.
@@ -277,8 +277,9 @@ typedef struct fw_batch_opts {
  * Allocates the device buffers for the call (two of B queries, one for a
  * single batch) and blocks until every row is in out_host; 16 MiB of pinned
  * staging and two streams stay with the graph until fw_graph_free (concurrent
- * calls on a graph make their own).  Errors: as fw_walk (start vertices are checked on the host
- * first), FW_EINVAL when the budget holds no query, FW_ENOMEM, FW_EHIP. */
+ * calls on a graph make their own).  Errors: as fw_walk (start vertices are
+ * checked on the host first), FW_EINVAL when the budget holds no query,
+ * FW_ENOMEM, FW_EHIP; rows not copied back by then keep what they held. */
 int fw_walk_host(const fw_graph* g, fw_algo algo, const fw_params* params,
                  const uint32_t* starts_host, uint64_t n, uint32_t length, uint64_t seed,
                  uint32_t* out_host, fw_batch_opts* opts);

@@ -125,7 +125,9 @@ __device__ __forceinline__ void wave_sync_lds() {
 // 1330 ms; Chung-Lu 227M node2vec, 1M queries, 7157, 7084, 7021 and 6992 ms.
 // With the hubs' totals kept, ratios 16, 32 and 64: 524,288 walks on R-MAT-22
 // 133.8, 128.0 and 128.6 ms, 200,003 unweighted walks of 40 hops on Chung-Lu
-// 2^20, whose rows stay in the last-level cache, 17.7, 17.7 and 18.4 ms.
+// 2^20, whose rows stay in the last-level cache, 17.7, 17.7 and 18.4 ms; ratios
+// 32 and 64: the first 1M queries of Chung-Lu 227M 3669 and 3576 ms.  32 is
+// within 3 % of the better one on each.
 constexpr uint64_t kSearchRatio = 32;
 
 struct Table {

@@ -321,15 +321,29 @@ hipError_t go(const LaunchArgs& a, unsigned block, hipStream_t stream) {
 }  // namespace
 
 // Queries per CU up to which a launch takes a workgroup per query.  Times of
-// 40 hops here and with a wavefront per query, us:
-//   R-MAT-20 (longest row 64 k), node2vec: 256 queries 289 and 977, 1,024 638
-//     and 1290, 3,001 1100 and 1383, 8,192 2031 and 1729; weighted DeepWalk:
-//     256 155 and 349, 2,048 247 and 361, 4,096 315 and 386;
-//   Chung-Lu 2^18, MetaPath: 256 140 and 170, 1,024 163 and 173, 2,048 210 and
-//     192;
-//   R-MAT-14 (no row past 8,192), node2vec: 256 194 and 299, 1,024 359 and 303;
-//     weighted DeepWalk: 256 118 and 115, 1,024 136 and 118.
-// Without long rows only node2vec gains, from the hash sets built ahead.
+// 40 hops here and with a wavefront per query (both forced), us:
+//   R-MAT-20 (longest row 64 k), node2vec: 512 queries 322 and 945, 1,024 473
+//     and 1071, 2,048 850 and 1116, 3,072 899 and 1180, 4,096 1002 and 1209,
+//     6,144 1433 and 1365; weighted DeepWalk: 512 173 and 236, 1,024 178 and
+//     235, 2,048 219 and 246, 3,072 251 and 246, 4,096 258 and 256, 6,144 365
+//     and 296; PPR: 1,024 85 and 100, 3,072 129 and 143, 6,144 159 and 167;
+//   Chung-Lu 2^18 (43 k), node2vec without weights: 512 279 and 514, 1,024 345
+//     and 564, 2,048 523 and 637, 3,072 743 and 669, 4,096 808 and 682;
+//     weighted DeepWalk: 1,024 166 and 207, 2,048 212 and 247, 3,072 257 and
+//     246, 4,096 327 and 263; MetaPath: 512 129 and 166, 1,024 139 and 164,
+//     2,048 206 and 180;
+//   R-MAT-14 (no row past 3,700), node2vec: 512 203 and 274, 768 224 and 286,
+//     1,024 225 and 288, 2,048 287 and 309, 3,072 411 and 327; weighted
+//     DeepWalk: 256 118 and 115, 1,024 136 and 118.
+// So on graphs with long rows both meet near twelve queries per CU (MetaPath:
+// between four and eight), a little earlier or later with the graph; without
+// them only node2vec gains, from the hash sets built ahead, clearly up to about
+// four.  Degrees between 3,700 and 43,000 were not timed.  A node2vec launch
+// here takes most of the LDS of the CUs it runs on and up to half of their
+// wavefronts, so launches on several streams overlap less: 256 queries each on
+// one, two and four streams, R-MAT-20 node2vec 270, 492 and 961 here against
+// 902, 959 and 1931, weighted DeepWalk 135, 251 and 462 against 227, 226 and
+// 253; R-MAT-14 node2vec 177, 334 and 643 against 264, 302 and 358.
 bool team_walks(const LaunchArgs& a) {
   const bool long_rows = a.max_deg > 8192;
   uint64_t per_cu = 0;
