@@ -275,9 +275,10 @@ typedef struct fw_batch_opts {
  *   out_host     host, uint32[n * (length + 1)], row-major as fw_walk's
  *   opts         may be NULL (defaults); receives B and the batch count
  * Allocates the device buffers for the call (two of B queries, one for a
- * single batch) and blocks until every row is in out_host; 16 MiB of pinned
- * staging and two streams stay with the graph until fw_graph_free (concurrent
- * calls on a graph make their own).  Errors: as fw_walk (start vertices are
+ * single batch) and blocks until every row is in out_host; up to 16 MiB of
+ * pinned staging, as much as the largest call's rows took, and two streams stay
+ * with the graph until fw_graph_free (concurrent calls on a graph make their
+ * own).  Errors: as fw_walk (start vertices are
  * checked on the host first), FW_EINVAL when the budget holds no query,
  * FW_ENOMEM, FW_EHIP; rows not copied back by then keep what they held. */
 int fw_walk_host(const fw_graph* g, fw_algo algo, const fw_params* params,

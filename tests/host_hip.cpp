@@ -33,6 +33,9 @@ std::map<const void*, std::string> names;
 std::vector<Launch> launches;
 std::atomic<long> fail_at{-1};  // this launch and those after it fail
 std::atomic<uintptr_t> handles{0x1000};
+std::map<void*, size_t> pinned;     // live pinned allocations
+std::atomic<size_t> pinned_made{0};  // bytes of all so far
+std::atomic<long> streams{0};        // live
 thread_local std::vector<Config> configs;
 thread_local hipError_t last_error = hipSuccess;
 
@@ -58,6 +61,14 @@ size_t host_hip_launches(Launch* out, size_t max, int clear) {
   for (size_t i = 0; i < n && i < max; ++i) out[i] = launches[i];
   if (clear) launches.clear();
   return n;
+}
+// Pinned bytes made so far and live now, live streams.
+void host_hip_pinned(size_t* made, size_t* live, long* live_streams) {
+  std::lock_guard<std::mutex> lk(mu);
+  *made = pinned_made;
+  *live = 0;
+  for (auto& p : pinned) *live += p.second;
+  *live_streams = streams;
 }
 // Launches fail from the k-th logged one on (-1: never).
 void host_hip_fail_at(long k) { fail_at = k; }
@@ -121,12 +132,19 @@ const char* hipGetErrorString(hipError_t) { return "host runtime error"; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 
 hipError_t hipMalloc(void** p, size_t n) { return memory(p, n); }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return memory(p, n); }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  const hipError_t e = memory(p, n);
+  std::lock_guard<std::mutex> lk(mu);
+  if (e == hipSuccess) pinned[*p] = n, pinned_made += n;
+  return e;
+}
 hipError_t hipFree(void* p) {
   std::free(p);
   return hipSuccess;
 }
 hipError_t hipHostFree(void* p) {
+  std::lock_guard<std::mutex> lk(mu);
+  pinned.erase(p);
   std::free(p);
   return hipSuccess;
 }
@@ -148,8 +166,14 @@ hipError_t hipMemset(void* d, int v, size_t n) {
 }
 hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { return hipMemset(d, v, n); }
 
-hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { return handle(s); }
-hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+  ++streams;
+  return handle(s);
+}
+hipError_t hipStreamDestroy(hipStream_t) {
+  --streams;
+  return hipSuccess;
+}
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) { return handle(e); }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return handle(e); }
